@@ -182,8 +182,8 @@ crf_status crf_validate_window(const crf_model_dims *dims, int32_t l0, int32_t h
  *                 window layer's output, and that layer's cache entry depends
  *                 on its input only through the K and V projections
  *                 (supplementary Eq. sup-layer-cache-dependency:
- *                 C_l = G_l(H_{l-1})), so on the bf16 path it runs RMSNorm and
- *                 the K/V projections (LoRA, bias, rotary, page write) only.
+ *                 C_l = G_l(H_{l-1})), so it runs RMSNorm and the K/V
+ *                 projections (LoRA, bias, rotary, page write) only.
  *                 The K/V written are the same either way.
  * h == 0 is direct reuse: nothing is launched and hidden_out (if given and
  * distinct) is not written.  Layers outside the window and pages outside the

@@ -42,9 +42,7 @@ struct crf_context {
   void *q = nullptr;       // [T, dq] rotated queries
   void *attn = nullptr;    // [T, dq] attention output
   void *act = nullptr;     // [T, f] SwiGLU output
-  void *u = nullptr;       // bf16: [T, 3*rank_pad] LoRA down-projections; fp32: [T, max_rank]
-  float *proj = nullptr;   // fp32 path: [T, dq + 2 dkv]
-  float *gu = nullptr;     // fp32 path: [T, 2f]
+  void *u = nullptr;       // bf16: [T, 3*rank_pad] LoRA down-projections; fp32: [T, 3*max_rank] past the fused ranks
   float2 *rope_cs = nullptr;
   int *d_err = nullptr;
   float *proj16 = nullptr;  // bf16 path, <= 16 token rows: fp32 Q/K/V projections [16, dq + 2 dkv]
@@ -348,7 +346,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
     // residual (the weight-streaming kernels of a few rows read the fp32 copy)
     const bool resid_from_boundary = first && !skinny;
     LAUNCH(ctx, s, CRF_KK_NORM,
-           launch_rmsnorm(s, first ? hb : (const void *)ctx->hres, !first, w.attn_norm, false, xn, false,
+           launch_rmsnorm(s, first ? hb : (const void *)ctx->hres, !first, w.attn_norm, xn,
                           first && !resid_from_boundary ? ctx->hres : nullptr, M, D, d.rms_eps));
     if (last && !hout && kv_tail) {
       // Nothing reads this layer's output: its cache entry depends only on its
@@ -420,7 +418,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
     }
     // MLP block
     LAUNCH(ctx, s, CRF_KK_NORM,
-           launch_rmsnorm(s, ctx->hres, true, w.mlp_norm, false, xn, false, nullptr, M, D, d.rms_eps));
+           launch_rmsnorm(s, ctx->hres, true, w.mlp_norm, xn, nullptr, M, D, d.rms_eps));
     any = lora_targets({CRF_GATE, CRF_UP}, tg);
     if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit));
     // the down projection's adapter down-projection rides on the gate/up
@@ -472,53 +470,98 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
   return CRF_OK;
 }
 
+// kv_tail: as for bf16, without hidden_out the last layer runs its K and V
+// projections only.
 crf_status run_layers_f32(crf_context *ctx, const void *hb, const crf_layer_weights *W, const crf_lora_layer *lora,
                           int l0, int h, const crf_kv_cache *kv, void *hout, hipStream_t s) {
   const crf_model_dims &d = ctx->dims;
   const int M = kv->n_tokens, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
-  const int PW = dq + 2 * dkv;
-  float *xn = (float *)ctx->xn, *q = (float *)ctx->q, *attn = (float *)ctx->attn, *act = (float *)ctx->act;
-  float *u = (float *)ctx->u;
-  // y[:, :] (ldc) += x W^T (+ scale (x A^T) B^T)
-  auto proj = [&](int l, int t, const float *x, int K, float *y, int ldc, float beta) -> crf_status {
-    int d_out, d_in;
-    target_shape(d, t, d_out, d_in);
-    const int kind = t <= CRF_V ? CRF_KK_GEMM_QKV
-                   : t == CRF_O ? CRF_KK_GEMM_O
-                   : t == CRF_DOWN ? CRF_KK_GEMM_DOWN : CRF_KK_GEMM_GATEUP;
-    LAUNCH(ctx, s, kind, launch_gemm_f32(s, M, d_out, K, x, K, (const float *)W[l].w[t], K, y, ldc, 1.f, beta));
-    if (has_lora(lora, l, t)) {
-      const int r = lora[l].rank;
-      LAUNCH(ctx, s, CRF_KK_LORA_DOWN,
-             launch_gemm_f32(s, M, r, K, x, K, (const float *)lora[l].A[t], K, u, r, lora[l].scale, 0.f));
-      LAUNCH(ctx, s, kind, launch_gemm_f32(s, M, d_out, r, u, r, (const float *)lora[l].B[t], r, y, ldc, 1.f, 1.f));
-    }
-    return CRF_OK;
-  };
-  crf_status st;
+  float *q = (float *)ctx->q, *attn = (float *)ctx->attn, *act = (float *)ctx->act, *u = (float *)ctx->u;
+  const float *x = (const float *)hb;  // the residual stream: the boundary state until the first update
   for (int l = l0; l < l0 + h; ++l) {
     const crf_layer_weights &w = W[l];
-    const bool first = l == l0;
-    LAUNCH(ctx, s, CRF_KK_NORM,
-           launch_rmsnorm(s, first ? hb : (const void *)ctx->hres, true, w.attn_norm, true, xn, true,
-                          first ? ctx->hres : nullptr, M, D, d.rms_eps));
-    if ((st = proj(l, CRF_Q, xn, D, ctx->proj, PW, 0.f)) != CRF_OK) return st;
-    if ((st = proj(l, CRF_K, xn, D, ctx->proj + dq, PW, 0.f)) != CRF_OK) return st;
-    if ((st = proj(l, CRF_V, xn, D, ctx->proj + dq + dkv, PW, 0.f)) != CRF_OK) return st;
-    const PagedKV pk = layer_kv(ctx, kv, l);
-    LAUNCH(ctx, s, CRF_KK_OTHER,
-           launch_qkv_post_f32(s, ctx->proj, (const float *)w.bias_q, (const float *)w.bias_k,
-                               (const float *)w.bias_v, q, pk, ctx->rope_cs, M, d.n_q_heads, d.n_kv_heads, hd));
-    LAUNCH(ctx, s, CRF_KK_ATTN, launch_attn_f32(s, q, pk, attn, M, d.n_q_heads, d.n_kv_heads, hd));
-    if ((st = proj(l, CRF_O, attn, dq, ctx->hres, D, 1.f)) != CRF_OK) return st;
-    LAUNCH(ctx, s, CRF_KK_NORM,
-           launch_rmsnorm(s, ctx->hres, true, w.mlp_norm, true, xn, true, nullptr, M, D, d.rms_eps));
-    if ((st = proj(l, CRF_GATE, xn, D, ctx->gu, 2 * f, 0.f)) != CRF_OK) return st;
-    if ((st = proj(l, CRF_UP, xn, D, ctx->gu + f, 2 * f, 0.f)) != CRF_OK) return st;
-    LAUNCH(ctx, s, CRF_KK_OTHER, launch_silu_mul_f32(s, ctx->gu, act, M, f));
-    if ((st = proj(l, CRF_DOWN, act, f, ctx->hres, D, 1.f)) != CRF_OK) return st;
+    const bool last = l == l0 + h - 1, kv_only = last && !hout;
+    const int rank = lora ? lora[l].rank : 0;
+    // segment i of a projection over targets t0, t0 + 1, ...
+    auto params = [&](const float *in, int K, const void *gain, int t0, int n_targets) {
+      F32Gemm p{};
+      p.x = in;
+      p.ldx = K;
+      p.M = M;
+      p.K = K;
+      p.gain = (const float *)gain;
+      p.eps = d.rms_eps;
+      p.rank = rank;
+      p.scale = lora ? lora[l].scale : 0.f;
+      p.U = u;
+      p.ldu = 3 * rank;
+      for (int i = 0; i < n_targets; ++i) {
+        int d_out, d_in;
+        target_shape(d, t0 + i, d_out, d_in);
+        p.w[i] = (const float *)w.w[t0 + i];
+        p.seg_rows[i] = d_out;
+        if (has_lora(lora, l, t0 + i)) {
+          p.la[i] = (const float *)lora[l].A[t0 + i];
+          p.lb[i] = (const float *)lora[l].B[t0 + i];
+        }
+      }
+      p.rope_cs = ctx->rope_cs;
+      p.hd = hd;
+      p.kv = layer_kv(ctx, kv, l);
+      return p;
+    };
+    auto project = [&](int kind, F32Epi epi, const F32Gemm &p) -> crf_status {
+      for (int i = 0; i < 3 && rank > F32_FUSED_RANK; ++i) {  // U of a larger rank: a pass of its own
+        if (!p.la[i]) continue;
+        F32Gemm pu = p;
+        pu.w[0] = p.la[i];
+        pu.seg_rows[0] = rank;
+        pu.out = u + i * rank;
+        pu.ldo = 3 * rank;
+        for (int j = 0; j < 3; ++j) pu.la[j] = pu.lb[j] = nullptr;
+        LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_gemm_f32(s, F32_PLAIN, pu));
+      }
+      LAUNCH(ctx, s, kind, launch_gemm_f32(s, epi, p));
+      return CRF_OK;
+    };
+    crf_status st;
+    {
+      F32Gemm p = params(x, D, w.attn_norm, CRF_Q, 3);
+      p.bias[0] = (const float *)w.bias_q;
+      p.bias[1] = (const float *)w.bias_k;
+      p.bias[2] = (const float *)w.bias_v;
+      p.seg1 = kv_only ? 0 : dq;
+      p.seg2 = p.seg1 + dkv;
+      p.N = p.seg2 + dkv;
+      if (kv_only) p.la[0] = p.lb[0] = nullptr;
+      p.out = q;
+      p.ldo = dq;
+      if ((st = project(CRF_KK_GEMM_QKV, F32_QKV, p)) != CRF_OK) return st;
+    }
+    if (kv_only) break;  // nothing reads this layer's output
+    LAUNCH(ctx, s, CRF_KK_ATTN, launch_attn_f32(s, q, layer_kv(ctx, kv, l), attn, M, d.n_q_heads, d.n_kv_heads, hd));
+    {
+      F32Gemm p = params(attn, dq, nullptr, CRF_O, 1);
+      p.resid_in = x;
+      p.out = ctx->hres;
+      p.ldo = D;
+      if ((st = project(CRF_KK_GEMM_O, F32_RESID, p)) != CRF_OK) return st;
+      x = ctx->hres;
+    }
+    {
+      F32Gemm p = params(x, D, w.mlp_norm, CRF_GATE, 2);
+      p.out = act;
+      p.ldo = f;
+      if ((st = project(CRF_KK_GEMM_GATEUP, F32_SWIGLU, p)) != CRF_OK) return st;
+    }
+    {
+      F32Gemm p = params(act, f, nullptr, CRF_DOWN, 1);
+      p.resid_in = x;
+      p.out = last ? (float *)hout : ctx->hres;
+      p.ldo = D;
+      if ((st = project(CRF_KK_GEMM_DOWN, F32_RESID, p)) != CRF_OK) return st;
+    }
   }
-  if (hout) HIP_TRY(ctx, hipMemcpyAsync(hout, ctx->hres, (size_t)M * D * sizeof(float), hipMemcpyDeviceToDevice, s));
   return CRF_OK;
 }
 
@@ -677,7 +720,7 @@ crf_status crf_validate_window(const crf_model_dims *dims, int32_t l0, int32_t h
 
 void crf_context_destroy(crf_context *ctx) {
   if (!ctx) return;
-  void *bufs[] = {ctx->hres, ctx->xn, ctx->q, ctx->attn, ctx->act, ctx->u, ctx->proj, ctx->gu, ctx->rope_cs,
+  void *bufs[] = {ctx->hres, ctx->xn, ctx->q, ctx->attn, ctx->act, ctx->u, ctx->rope_cs,
                   ctx->d_err, ctx->drift_dev, ctx->proj16, ctx->attn_part, ctx->lora_part, ctx->gemm_part,
                   ctx->dn_part, ctx->dn_head};
   for (void *b : bufs)
@@ -719,7 +762,7 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
     return s;
   };
   if ((st = dmalloc(ctx, &ctx->hres, T * D * 4)) != CRF_OK) return cleanup(st);
-  if ((st = dmalloc(ctx, &ctx->xn, T * D * e)) != CRF_OK) return cleanup(st);
+  if (dims->dtype == CRF_BF16 && (st = dmalloc(ctx, &ctx->xn, T * D * e)) != CRF_OK) return cleanup(st);
   if ((st = dmalloc(ctx, &ctx->q, T * dq * e)) != CRF_OK) return cleanup(st);
   if ((st = dmalloc(ctx, &ctx->attn, T * dq * e)) != CRF_OK) return cleanup(st);
   if ((st = dmalloc(ctx, &ctx->act, T * f * e)) != CRF_OK) return cleanup(st);
@@ -748,10 +791,8 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
         return cleanup(st);
     }
   } else {
-    if ((st = dmalloc(ctx, &ctx->u, T * (size_t)(max_lora_rank > 0 ? max_lora_rank : 1) * 4)) != CRF_OK)
-      return cleanup(st);
-    if ((st = dmalloc(ctx, &ctx->proj, T * (dq + 2 * dkv) * 4)) != CRF_OK) return cleanup(st);
-    if ((st = dmalloc(ctx, &ctx->gu, T * 2 * f * 4)) != CRF_OK) return cleanup(st);
+    const size_t ur = max_lora_rank > F32_FUSED_RANK ? 3 * (size_t)max_lora_rank : 0;
+    if ((st = dmalloc(ctx, &ctx->u, T * ur * 4)) != CRF_OK) return cleanup(st);
   }
   if ((st = dmalloc(ctx, &ctx->rope_cs, T * (dims->head_dim / 2) * sizeof(float2))) != CRF_OK) return cleanup(st);
   if ((st = dmalloc(ctx, &ctx->d_err, sizeof(int))) != CRF_OK) return cleanup(st);
@@ -907,7 +948,7 @@ crf_status crf_decode_logits(crf_context *ctx, const crf_model_dims *dims, const
   // final RMSNorm of the last new token (fp32 residual stream) and the LM head
   const size_t D = d.d_model;
   LAUNCH(ctx, s, CRF_KK_NORM,
-         launch_rmsnorm(s, ctx->hres + (size_t)(n_new - 1) * D, true, final_norm, false, ctx->xn, false, nullptr, 1,
+         launch_rmsnorm(s, ctx->hres + (size_t)(n_new - 1) * D, true, final_norm, (bf16 *)ctx->xn, nullptr, 1,
                         (int)D, d.rms_eps));
   GemmParams p{};
   p.X = (const bf16 *)ctx->xn;

@@ -8,22 +8,48 @@
 namespace crf {
 
 // ---------------------------------------------------------------- shared
-// y = g * x / sqrt(mean(x^2) + eps) row-wise over d; x fp32 or bf16, y fp32 or
-// bf16, g in the model dtype.  copy_out (nullable) receives x as fp32.
-hipError_t launch_rmsnorm(hipStream_t s, const void *x, bool x_f32, const void *g, bool g_f32, void *y,
-                          bool y_f32, float *copy_out, int M, int d, float eps);
+// y = g * x / sqrt(mean(x^2) + eps) row-wise over d; x fp32 or bf16, y and g
+// bf16.  copy_out (nullable) receives x as fp32.
+hipError_t launch_rmsnorm(hipStream_t s, const void *x, bool x_f32, const void *g, bf16 *y, float *copy_out, int M,
+                          int d, float eps);
 // cos/sin table cs[p*hd/2 + i] = (cos, sin)(p * theta^(-2i/hd)), angles in fp64.
 hipError_t launch_rope_table(hipStream_t s, float2 *cs, int T, int hd, float theta);
 
 // ---------------------------------------------------------------- fp32 path
-// C = alpha * A B^T + beta * C with A [M,K] (lda), B [N,K] (ldb), C [M,N] (ldc).
-hipError_t launch_gemm_f32(hipStream_t s, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
-                           float *C, int ldc, float alpha, float beta);
-// P [M, dq+2dkv] -> Q (rotated) [M, dq], K (rotated) and V written to pages.
-hipError_t launch_qkv_post_f32(hipStream_t s, const float *P, const float *bq, const float *bk, const float *bv,
-                               float *Q, const PagedKV &kv, const float2 *cs, int M, int nq, int nkv, int hd);
-// act[m, f] = silu(G[m, f]) * U[m, f] with G = GU[:, :f], U = GU[:, f:2f].
-hipError_t launch_silu_mul_f32(hipStream_t s, const float *GU, float *act, int M, int f);
+enum F32Epi { F32_QKV = 0, F32_RESID = 1, F32_SWIGLU = 2, F32_PLAIN = 3 };
+// adapters up to this rank are formed inside the projection (one 16-row block)
+constexpr int F32_FUSED_RANK = 16;
+// Y = norm(x) W^T + adapter with one of the epilogues:
+//   F32_QKV    rows [0, seg1) Q, [seg1, seg2) K, [seg2, N) V: bias, rotation, Q
+//              to out, K and V to the pages of kv;
+//   F32_RESID  out = resid_in + Y (either may be the other);
+//   F32_SWIGLU out = silu(Y_0) * Y_1 of segments 0 (gate) and 1 (up);
+//   F32_PLAIN  out = scale * Y (an adapter's U, for ranks past F32_FUSED_RANK).
+struct F32Gemm {
+  const float *x;
+  int64_t ldx;
+  int M, K, N;
+  const float *gain;       // RMSNorm gain of x (nullable: x as it is), with eps
+  float eps;
+  const float *w[3];       // [seg_rows, K]
+  int seg_rows[3];
+  int seg1, seg2;
+  // adapter of segment s: la [rank, K], lb [seg_rows, rank] (both null: none);
+  // past F32_FUSED_RANK U [M, ldu] holds segment s's scaled U at column s * rank
+  const float *la[3], *lb[3];
+  int rank;
+  float scale;
+  const float *U;
+  int ldu;
+  float *out;
+  int64_t ldo;
+  const float *resid_in;
+  const float *bias[3];
+  const float2 *rope_cs;
+  PagedKV kv;
+  int hd;
+};
+hipError_t launch_gemm_f32(hipStream_t s, F32Epi epi, const F32Gemm &p);
 hipError_t launch_attn_f32(hipStream_t s, const float *Q, const PagedKV &kv, float *O, int M, int nq, int nkv,
                            int hd);
 

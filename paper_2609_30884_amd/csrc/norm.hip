@@ -5,13 +5,6 @@ namespace crf {
 namespace {
 
 template <typename T>
-CRF_DEV float ldf(const T *p, int64_t i);
-template <>
-CRF_DEV float ldf<float>(const float *p, int64_t i) { return p[i]; }
-template <>
-CRF_DEV float ldf<bf16>(const bf16 *p, int64_t i) { return bf2f(p[i]); }
-
-template <typename T>
 CRF_DEV void load8(const T *p, float (&v)[8]);
 template <>
 CRF_DEV void load8<float>(const float *p, float (&v)[8]) {
@@ -42,9 +35,9 @@ CRF_DEV void store8<bf16>(bf16 *p, const float (&v)[8]) {
 }
 
 // One wave per row; 4 rows per workgroup.  d must be a multiple of 8.
-template <typename TX, typename TG, typename TY>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const TX *__restrict__ x, const TG *__restrict__ g,
-                                                      TY *__restrict__ y, float *__restrict__ copy_out, int M,
+template <typename TX>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const TX *__restrict__ x, const bf16 *__restrict__ g,
+                                                      bf16 *__restrict__ y, float *__restrict__ copy_out, int M,
                                                       int d, float eps) {
   const int row = blockIdx.x * 4 + threadIdx.x / 64;
   const int lane = threadIdx.x % 64;
@@ -74,9 +67,9 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const TX *__restrict__ x, 
 // elements [512 c + 8 l, 512 c + 8 l + 8) of chunk c < NCH, d <= 512 NCH.  All
 // of a wave's loads are issued before the first use, so a row's bytes are in
 // flight at once.
-template <typename TX, typename TG, typename TY, int NCH>
-__global__ __launch_bounds__(256) void rmsnorm_reg_kernel(const TX *__restrict__ x, const TG *__restrict__ g,
-                                                          TY *__restrict__ y, float *__restrict__ copy_out, int M,
+template <typename TX, int NCH>
+__global__ __launch_bounds__(256) void rmsnorm_reg_kernel(const TX *__restrict__ x, const bf16 *__restrict__ g,
+                                                          bf16 *__restrict__ y, float *__restrict__ copy_out, int M,
                                                           int d, float eps) {
   const int row = blockIdx.x * 4 + threadIdx.x / 64;
   const int lane = threadIdx.x % 64;
@@ -123,37 +116,32 @@ __global__ void rope_table_kernel(float2 *cs, int T, int hd, double log_theta) {
   cs[idx] = make_float2((float)cos(phi), (float)sin(phi));
 }
 
-template <typename TX, typename TG, typename TY>
-hipError_t go(hipStream_t s, const void *x, const void *g, void *y, float *copy_out, int M, int d, float eps) {
+template <typename TX>
+hipError_t go(hipStream_t s, const void *x, const void *g, bf16 *yp, float *copy_out, int M, int d, float eps) {
   if (M <= 0) return hipSuccess;
   const dim3 grid((M + 3) / 4), block(256);
   const TX *xp = (const TX *)x;
-  const TG *gp = (const TG *)g;
-  TY *yp = (TY *)y;
+  const bf16 *gp = (const bf16 *)g;
   switch ((d + 511) / 512) {
 #define CRF_NORM_CASE(n)                                                                                   \
   case n:                                                                                                  \
-    hipLaunchKernelGGL((rmsnorm_reg_kernel<TX, TG, TY, n>), grid, block, 0, s, xp, gp, yp, copy_out, M, d, eps); \
+    hipLaunchKernelGGL((rmsnorm_reg_kernel<TX, n>), grid, block, 0, s, xp, gp, yp, copy_out, M, d, eps); \
     break;
     CRF_NORM_CASE(1) CRF_NORM_CASE(2) CRF_NORM_CASE(3) CRF_NORM_CASE(4) CRF_NORM_CASE(5) CRF_NORM_CASE(6)
     CRF_NORM_CASE(7) CRF_NORM_CASE(8) CRF_NORM_CASE(9) CRF_NORM_CASE(10) CRF_NORM_CASE(11) CRF_NORM_CASE(12)
     CRF_NORM_CASE(13) CRF_NORM_CASE(14) CRF_NORM_CASE(15) CRF_NORM_CASE(16)
 #undef CRF_NORM_CASE
     default:  // wider rows: two passes over the row
-      hipLaunchKernelGGL((rmsnorm_kernel<TX, TG, TY>), grid, block, 0, s, xp, gp, yp, copy_out, M, d, eps);
+      hipLaunchKernelGGL((rmsnorm_kernel<TX>), grid, block, 0, s, xp, gp, yp, copy_out, M, d, eps);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_rmsnorm(hipStream_t s, const void *x, bool x_f32, const void *g, bool g_f32, void *y, bool y_f32,
-                          float *copy_out, int M, int d, float eps) {
-  if (x_f32 && g_f32 && y_f32) return go<float, float, float>(s, x, g, y, copy_out, M, d, eps);
-  if (x_f32 && !g_f32 && !y_f32) return go<float, bf16, bf16>(s, x, g, y, copy_out, M, d, eps);
-  if (!x_f32 && !g_f32 && !y_f32) return go<bf16, bf16, bf16>(s, x, g, y, copy_out, M, d, eps);
-  if (!x_f32 && g_f32 && y_f32) return go<bf16, float, float>(s, x, g, y, copy_out, M, d, eps);
-  return hipErrorInvalidValue;
+hipError_t launch_rmsnorm(hipStream_t s, const void *x, bool x_f32, const void *g, bf16 *y, float *copy_out, int M,
+                          int d, float eps) {
+  return x_f32 ? go<float>(s, x, g, y, copy_out, M, d, eps) : go<bf16>(s, x, g, y, copy_out, M, d, eps);
 }
 
 hipError_t launch_rope_table(hipStream_t s, float2 *cs, int T, int hd, float theta) {
