@@ -282,8 +282,9 @@ crf_status crf_layer_drift(crf_context *ctx, const crf_model_dims *dims, const c
  * memory on `stream` (so the call returns once they are copied).  Calls that
  * overlap on one device race on its scratch: serialise them (one stream, or
  * the caller's own ordering).  A request whose tables and partials exceed the
- * scratch (segments: two per adapter target, layer and version; chunks of 2^16
- * elements each; about 64 bytes per chunk and segment) is rejected with
+ * scratch (segments: two per adapter target and layer; chunks of 2^13 to 2^16
+ * elements each; per segment and per chunk about 16 bytes and 8 for each
+ * version) is rejected with
  * WORKSPACE before anything is copied or launched.  Errors are reported through
  * crf_last_error(NULL): INVALID_ARG, SHAPE, UNSUPPORTED (as crf_validate_dims),
  * WORKSPACE, HIP. */

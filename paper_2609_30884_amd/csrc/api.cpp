@@ -25,6 +25,14 @@ struct Timer {
   size_t used = 0;              // pairs recorded since last read
 };
 
+// Pinned host staging of the drift tables of one call; `ev` marks their copy.
+struct DriftStage {
+  void *host = nullptr;
+  size_t bytes = 0;
+  hipEvent_t ev = nullptr;
+  bool recorded = false;
+};
+
 }  // namespace
 
 // runs of consecutive gate/up tiles on one token tile per workgroup whose fused
@@ -56,12 +64,10 @@ struct crf_context {
   int *dn_head = nullptr;      //   and the table of their first tiles
   int n_cu = 0;
   // drift staging
-  void *drift_host = nullptr;
-  size_t drift_host_bytes = 0;
+  DriftStage drift_stage[4];
+  unsigned drift_next = 0;  // stage of the next call
   void *drift_dev = nullptr;
   size_t drift_dev_bytes = 0;
-  hipEvent_t drift_ev = nullptr;
-  bool drift_ev_recorded = false;
   std::string last_error;
   Timer timer;
   // batched calls over independent caches: a second workspace (a context of
@@ -586,18 +592,22 @@ crf_status dmalloc(crf_context *ctx, T **p, size_t bytes) {
 
 namespace {
 
-// Drift tables: segments (one per current/version factor pair), chunks of at
-// most 2^16 elements, and per (version, layer) the first chunk and the chunk
-// count.  Staging layout: segs | chunks | first | count | anchor, copied from
-// the host, then partials (double, one per chunk) and scratch (double, one per
-// (version, layer)) written by the kernels.
-constexpr int64_t DRIFT_CHUNK = 1 << 16;
+// Drift tables: segments (one per factor tensor of the current adapter), the
+// stored versions' pointers per segment, chunks (layer by layer), the first
+// chunk of each layer, the anchors and the ticket, copied from the host in one
+// block; then partials (double, one per version and chunk) and squared
+// distances (double, one per version and layer) written by the kernel.
+// Chunks are as small as keeps their number moderate: 8192 elements fill the
+// GPU at adapters of a few million parameters (one workgroup reads 16 KB per
+// tensor), and an adapter ten times that has enough of the larger ones.
+constexpr int DRIFT_CHUNK_MIN = 1 << 13, DRIFT_CHUNK_MAX = 1 << 16;
+constexpr size_t DRIFT_MAX_CHUNKS = 8192;
 
 struct DriftPlan {
-  int L = 0, V = 0;
+  int L = 0, V = 0, chunk = 0;
   size_t n_segs = 0, n_chunks = 0;
-  size_t o_segs = 0, o_chunks = 0, o_first = 0, o_count = 0, o_anchor = 0, host_bytes = 0, o_part = 0, o_scr = 0,
-         dev_bytes = 0;
+  size_t o_segs = 0, o_b = 0, o_chunks = 0, o_first = 0, o_anchor = 0, o_ticket = 0, host_bytes = 0, o_part = 0,
+         o_sq = 0, dev_bytes = 0;
 };
 
 // Validates a drift request and sizes its tables (touches no device).
@@ -622,27 +632,38 @@ crf_status drift_plan(crf_context *ctx, const crf_model_dims *dims, const crf_lo
         if (!c.A[t]) continue;
         if (!c.B[t] || !vv.A[t] || !vv.B[t] || vv.rank != c.rank)
           return fail(ctx, CRF_ERR_INVALID_ARG, "layer %d target %d missing or rank differs in version %d", l, t, v);
-        int d_out, d_in;
-        target_shape(*dims, t, d_out, d_in);
-        const int64_t cnt[2] = {(int64_t)c.rank * d_in, (int64_t)d_out * c.rank};
-        for (int k = 0; k < 2; ++k) {
-          ++pl.n_segs;
-          pl.n_chunks += (size_t)((cnt[k] + DRIFT_CHUNK - 1) / DRIFT_CHUNK);
-        }
       }
     }
   }
-  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const size_t n_out = (size_t)n_versions * L;
-  pl.o_segs = 0;
-  pl.o_chunks = al(pl.o_segs + pl.n_segs * sizeof(DriftSeg));
-  pl.o_first = al(pl.o_chunks + pl.n_chunks * sizeof(DriftChunk));
-  pl.o_count = al(pl.o_first + n_out * sizeof(int));
-  pl.o_anchor = al(pl.o_count + n_out * sizeof(int));
-  pl.host_bytes = al(pl.o_anchor + L * sizeof(int));
-  pl.o_part = pl.host_bytes;
-  pl.o_scr = al(pl.o_part + (pl.n_chunks + 1) * sizeof(double));
-  pl.dev_bytes = al(pl.o_scr + n_out * sizeof(double));
+  for (pl.chunk = DRIFT_CHUNK_MIN;; pl.chunk *= 2) {
+    pl.n_segs = pl.n_chunks = 0;
+    for (int l = 0; l < L; ++l)
+      for (int t = 0; t < CRF_NUM_TARGETS && current[l].rank > 0; ++t) {
+        if (!current[l].A[t]) continue;
+        int d_out, d_in;
+        target_shape(*dims, t, d_out, d_in);
+        for (int64_t cnt : {(int64_t)current[l].rank * d_in, (int64_t)d_out * current[l].rank}) {
+          ++pl.n_segs;
+          pl.n_chunks += (size_t)((cnt + pl.chunk - 1) / pl.chunk);
+        }
+      }
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t V = (size_t)n_versions;
+    pl.o_segs = 0;
+    pl.o_b = al(pl.o_segs + pl.n_segs * sizeof(DriftSeg));
+    pl.o_chunks = al(pl.o_b + pl.n_segs * V * sizeof(void *));
+    pl.o_first = al(pl.o_chunks + pl.n_chunks * sizeof(DriftChunk));
+    pl.o_anchor = pl.o_first + ((size_t)L + 1) * sizeof(int);
+    pl.o_ticket = pl.o_anchor + (size_t)L * sizeof(int);
+    pl.host_bytes = al(pl.o_ticket + sizeof(unsigned));
+    pl.o_part = pl.host_bytes;
+    pl.o_sq = al(pl.o_part + V * pl.n_chunks * sizeof(double));
+    pl.dev_bytes = al(pl.o_sq + V * L * sizeof(double));
+    // (with and without a context alike, so that both sum in the same order)
+    if (pl.chunk >= DRIFT_CHUNK_MAX ||
+        (pl.n_chunks <= DRIFT_MAX_CHUNKS && pl.dev_bytes <= CRF_DRIFT_NOALLOC_MAX_BYTES))
+      break;
+  }
   return CRF_OK;
 }
 
@@ -650,42 +671,54 @@ crf_status drift_plan(crf_context *ctx, const crf_model_dims *dims, const crf_lo
 void drift_fill(const DriftPlan &pl, const crf_model_dims *dims, const crf_lora_layer *current,
                 const crf_lora_layer *const *versions, const int32_t *anchor_version, char *hb) {
   DriftSeg *segs = (DriftSeg *)(hb + pl.o_segs);
+  const void **b = (const void **)(hb + pl.o_b);
   DriftChunk *chunks = (DriftChunk *)(hb + pl.o_chunks);
-  int *first = (int *)(hb + pl.o_first), *count = (int *)(hb + pl.o_count);
+  int *first = (int *)(hb + pl.o_first);
   int ns = 0, nc = 0;
-  for (int v = 0; v < pl.V; ++v)
-    for (int l = 0; l < pl.L; ++l) {
-      const int o = v * pl.L + l;
-      first[o] = nc;
-      const crf_lora_layer &c = current[l], &vv = versions[v][l];
-      for (int t = 0; t < CRF_NUM_TARGETS && c.rank > 0; ++t) {
-        if (!c.A[t]) continue;
-        int d_out, d_in;
-        target_shape(*dims, t, d_out, d_in);
-        const int64_t cnt[2] = {(int64_t)c.rank * d_in, (int64_t)d_out * c.rank};
-        const void *pa[2] = {c.A[t], c.B[t]}, *pb[2] = {vv.A[t], vv.B[t]};
-        for (int k = 0; k < 2; ++k) {
-          const int si = ns++;
-          segs[si] = DriftSeg{pa[k], pb[k], cnt[k], o};
-          for (int64_t s0 = 0; s0 < cnt[k]; s0 += DRIFT_CHUNK)
-            chunks[nc++] = DriftChunk{si, s0, std::min(DRIFT_CHUNK, cnt[k] - s0)};
-        }
+  for (int l = 0; l < pl.L; ++l) {
+    first[l] = nc;
+    const crf_lora_layer &c = current[l];
+    for (int t = 0; t < CRF_NUM_TARGETS && c.rank > 0; ++t) {
+      if (!c.A[t]) continue;
+      int d_out, d_in;
+      target_shape(*dims, t, d_out, d_in);
+      const int64_t cnt[2] = {(int64_t)c.rank * d_in, (int64_t)d_out * c.rank};
+      for (int k = 0; k < 2; ++k) {
+        segs[ns] = DriftSeg{k ? c.B[t] : c.A[t], cnt[k]};
+        for (int v = 0; v < pl.V; ++v)
+          b[(size_t)ns * pl.V + v] = k ? versions[v][l].B[t] : versions[v][l].A[t];
+        for (int i = 0; (int64_t)i * pl.chunk < cnt[k]; ++i) chunks[nc++] = DriftChunk{ns, i};
+        ++ns;
       }
-      count[o] = nc - first[o];
     }
+  }
+  first[pl.L] = nc;
   memcpy(hb + pl.o_anchor, anchor_version, pl.L * sizeof(int));
+  *(unsigned *)(hb + pl.o_ticket) = 0;
 }
 
-// The two drift kernels over staging db (tables already there).
+// The drift kernel over staging db (tables already there).
 hipError_t drift_launch(hipStream_t s, const DriftPlan &pl, char *db, bool f32, const float *sensitivity,
                         int32_t per_layer_only, float *drift_out, float *risk_out, float *sq_partial_out) {
-  hipError_t e = launch_drift_partials(s, (const DriftSeg *)(db + pl.o_segs), (const DriftChunk *)(db + pl.o_chunks),
-                                       (int)pl.n_chunks, f32, (double *)(db + pl.o_part));
-  if (e != hipSuccess) return e;
-  return launch_drift_finalize(s, (const double *)(db + pl.o_part), (const int *)(db + pl.o_first),
-                               (const int *)(db + pl.o_count), pl.V, pl.L, (const int *)(db + pl.o_anchor),
-                               sensitivity, per_layer_only, drift_out, risk_out, sq_partial_out,
-                               (double *)(db + pl.o_scr));
+  DriftArgs a{};
+  a.segs = (const DriftSeg *)(db + pl.o_segs);
+  a.b = (const void *const *)(db + pl.o_b);
+  a.chunks = (const DriftChunk *)(db + pl.o_chunks);
+  a.n_chunks = (int)pl.n_chunks;
+  a.chunk = pl.chunk;
+  a.first = (const int *)(db + pl.o_first);
+  a.anchor = (const int *)(db + pl.o_anchor);
+  a.n_versions = pl.V;
+  a.n_layers = pl.L;
+  a.ticket = (unsigned *)(db + pl.o_ticket);
+  a.partials = (double *)(db + pl.o_part);
+  a.sq = (double *)(db + pl.o_sq);
+  a.sens = sensitivity;
+  a.per_layer_only = per_layer_only;
+  a.drift = drift_out;
+  a.risk = risk_out;
+  a.sq_out = sq_partial_out;
+  return launch_drift(s, f32, a);
 }
 
 }  // namespace
@@ -725,8 +758,10 @@ void crf_context_destroy(crf_context *ctx) {
                   ctx->dn_part, ctx->dn_head};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
-  if (ctx->drift_host) (void)hipHostFree(ctx->drift_host);
-  if (ctx->drift_ev) (void)hipEventDestroy(ctx->drift_ev);
+  for (DriftStage &st : ctx->drift_stage) {
+    if (st.host) (void)hipHostFree(st.host);
+    if (st.ev) (void)hipEventDestroy(st.ev);
+  }
   for (hipEvent_t e : ctx->timer.ev) (void)hipEventDestroy(e);
   for (int i = 0; i < 2; ++i) {
     if (ctx->lane_s[i]) (void)hipStreamDestroy(ctx->lane_s[i]);
@@ -976,14 +1011,17 @@ crf_status crf_layer_drift(crf_context *ctx, const crf_model_dims *dims, const c
   if ((st = drift_plan(ctx, dims, current, n_versions, versions, anchor_version, drift_out, risk_out, pl)) != CRF_OK)
     return st;
   hipStream_t s = (hipStream_t)stream;
-  if (!ctx->drift_ev) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->drift_ev, hipEventDisableTiming));
-  if (ctx->drift_ev_recorded) HIP_TRY(ctx, hipEventSynchronize(ctx->drift_ev));
-  if (pl.host_bytes > ctx->drift_host_bytes) {
-    if (ctx->drift_host) HIP_TRY(ctx, hipHostFree(ctx->drift_host));
-    ctx->drift_host = nullptr;
-    ctx->drift_host_bytes = 0;
-    HIP_TRY(ctx, hipHostMalloc(&ctx->drift_host, pl.host_bytes, hipHostMallocDefault));
-    ctx->drift_host_bytes = pl.host_bytes;
+  // a few calls' tables may be on their way at once, so that the host builds
+  // the next call's while the GPU is still at the last one
+  DriftStage &sg = ctx->drift_stage[ctx->drift_next++ % 4];
+  if (!sg.ev) HIP_TRY(ctx, hipEventCreateWithFlags(&sg.ev, hipEventDisableTiming));
+  if (sg.recorded) HIP_TRY(ctx, hipEventSynchronize(sg.ev));
+  if (pl.host_bytes > sg.bytes) {
+    if (sg.host) HIP_TRY(ctx, hipHostFree(sg.host));
+    sg.host = nullptr;
+    sg.bytes = 0;
+    HIP_TRY(ctx, hipHostMalloc(&sg.host, pl.host_bytes, hipHostMallocDefault));
+    sg.bytes = pl.host_bytes;
   }
   if (pl.dev_bytes > ctx->drift_dev_bytes) {
     HIP_TRY(ctx, hipStreamSynchronize(s));
@@ -993,11 +1031,11 @@ crf_status crf_layer_drift(crf_context *ctx, const crf_model_dims *dims, const c
     HIP_TRY(ctx, hipMalloc(&ctx->drift_dev, pl.dev_bytes));
     ctx->drift_dev_bytes = pl.dev_bytes;
   }
-  char *hb = (char *)ctx->drift_host, *db = (char *)ctx->drift_dev;
+  char *hb = (char *)sg.host, *db = (char *)ctx->drift_dev;
   drift_fill(pl, dims, current, versions, anchor_version, hb);
   HIP_TRY(ctx, hipMemcpyAsync(db, hb, pl.host_bytes, hipMemcpyHostToDevice, s));
-  HIP_TRY(ctx, hipEventRecord(ctx->drift_ev, s));
-  ctx->drift_ev_recorded = true;
+  HIP_TRY(ctx, hipEventRecord(sg.ev, s));
+  sg.recorded = true;
   LAUNCH(ctx, s, CRF_KK_DRIFT,
          drift_launch(s, pl, db, dims->dtype == CRF_F32, sensitivity, per_layer_only, drift_out, risk_out,
                       sq_partial_out));

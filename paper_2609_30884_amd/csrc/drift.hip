@@ -1,7 +1,17 @@
-// Adapter drift: squared distances between the current adapter and stored
-// versions, chunked over all (version, layer, target, factor) segments, then
-// reduced in a fixed order (deterministic).  Accumulation in fp64.
+// Adapter drift: squared distances between the current adapter and every stored
+// version, in chunks of its factor tensors, then summed in a fixed order
+// (deterministic).  Accumulation in fp64.
+//
+// HBM-bound once enough bytes are in flight: a workgroup reads its chunk of the
+// current adapter once for four versions, 16 bytes per lane and four loads per
+// tensor ahead of the sums, and the workgroup that finishes last forms the
+// outputs, so that there is no second launch.  Measured: 28 layers x 4 versions at 1.5B shapes
+// (44 MB) 32 + 5 -> 20 us on the GPU, 56 -> 25 us a call; x 2 versions at 7B
+// shapes (242 MB) 85 + 8 -> 51 us (4.7 TB/s), 153 -> 66 us a call.  The first
+// is all latency: tables, chunk, and the last workgroup's two rounds of loads.
 #include <math.h>
+
+#include <algorithm>
 
 #include <mutex>
 
@@ -23,61 +33,171 @@ CRF_DEV double tod<float>(float x) { return (double)x; }
 template <>
 CRF_DEV double tod<bf16>(bf16 x) { return (double)bf2f(x); }
 
+// Partials cross workgroups (and XCDs, whose L2 caches are not coherent with
+// each other) as agent-scope accesses, which go to memory.
+CRF_DEV void st_agent(double *p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+CRF_DEV double ld_agent(const double *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+CRF_DEV double sum16(double v) {  // over 16 consecutive lanes, in every lane
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
+  return v;
+}
+
 template <typename T>
-__global__ __launch_bounds__(256) void drift_partials_kernel(const DriftSeg *__restrict__ segs,
-                                                             const DriftChunk *__restrict__ chunks,
-                                                             double *__restrict__ partials) {
-  __shared__ double red[256];
-  const DriftChunk ch = chunks[blockIdx.x];
-  const DriftSeg sg = segs[ch.seg];
-  const T *a = (const T *)sg.a + ch.start;
-  const T *b = (const T *)sg.b + ch.start;
-  double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < ch.len; i += 256) {
-    const double d = tod<T>(a[i]) - tod<T>(b[i]);
+CRF_DEV void add_vec(double &acc, u32x4 a, u32x4 b) {
+  constexpr int VE = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(VE)));
+  const vec av = __builtin_bit_cast(vec, a), bv = __builtin_bit_cast(vec, b);
+#pragma unroll
+  for (int e = 0; e < VE; ++e) {
+    const double d = tod<T>(av[e]) - tod<T>(bv[e]);
     acc = fma(d, d, acc);
   }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
 }
 
-// Single workgroup: sq[o] = sum of its chunks (in order); then per layer l
-// d_l = sqrt(sum_l' sq[anchor(l), l'])  (or sqrt(sq[anchor(l), l]) per layer).
-__global__ __launch_bounds__(256) void drift_finalize_kernel(const double *__restrict__ partials,
-                                                             const int *__restrict__ chunk_first,
-                                                             const int *__restrict__ chunk_count, int n_versions,
-                                                             int n_layers, const int *__restrict__ anchor,
-                                                             const float *__restrict__ sens, int per_layer_only,
-                                                             float *drift, float *risk, float *sq_out,
-                                                             double *scratch) {
-  const int n_out = n_versions * n_layers;
-  for (int o = threadIdx.x; o < n_out; o += 256) {
-    double s = 0.0;
-    for (int c = 0; c < chunk_count[o]; ++c) s += partials[chunk_first[o] + c];
-    scratch[o] = s;
-    if (sq_out) sq_out[o] = (float)s;
+constexpr int SQ_LDS = 512;  // squared distances the last workgroup keeps at hand
+
+template <typename T>
+__global__ __launch_bounds__(256) void drift_kernel(const DriftArgs p) {
+  constexpr int VE = 16 / sizeof(T);  // elements per load
+  constexpr int VB = 4, UN = 4;       // versions and loads per tensor in flight
+  __shared__ double red[4][VB];
+  __shared__ bool is_last;
+  __shared__ double sq_lds[SQ_LDS];
+  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+  // (the next chunk's descriptors are read one chunk ahead)
+  DriftChunk ch{}, chn{};
+  DriftSeg sg{}, sgn{};
+  if ((int)blockIdx.x < p.n_chunks) {
+    chn = p.chunks[blockIdx.x];
+    sgn = p.segs[chn.seg];
   }
-  __syncthreads();
-  for (int l = threadIdx.x; l < n_layers; l += 256) {
-    const int v = anchor[l];
-    double s;
-    if (per_layer_only) {
-      s = scratch[v * n_layers + l];
-    } else {
-      s = 0.0;
-      for (int k = 0; k < n_layers; ++k) s += scratch[v * n_layers + k];
+  for (int c = blockIdx.x; c < p.n_chunks; c += gridDim.x) {
+    ch = chn;
+    sg = sgn;
+    if (c + (int)gridDim.x < p.n_chunks) {
+      chn = p.chunks[c + gridDim.x];
+      sgn = p.segs[chn.seg];
     }
-    const double d = sqrt(s);
-    drift[l] = (float)d;
-    risk[l] = (float)(d * (sens ? (double)sens[l] : 1.0));
+    const int64_t start = (int64_t)ch.idx * p.chunk;
+    const int len = (int)min((int64_t)p.chunk, sg.count - start);
+    const T *a = (const T *)sg.a + start;
+    for (int v0 = 0; v0 < p.n_versions; v0 += VB) {
+      const T *b[VB];
+      uintptr_t bits = (uintptr_t)a;
+#pragma unroll
+      for (int v = 0; v < VB; ++v) {  // a version past the last repeats it (its sum is dropped)
+        b[v] = (const T *)p.b[(int64_t)ch.seg * p.n_versions + min(v0 + v, p.n_versions - 1)] + start;
+        bits |= (uintptr_t)b[v];
+      }
+      const int nv = min(VB, p.n_versions - v0);
+      double acc[VB] = {0.0, 0.0, 0.0, 0.0};
+      int done = 0;  // elements summed by the vector loop
+      if ((bits & 15) == 0) {
+        const int nvec = len / VE;
+        for (int i0 = 0; i0 < nvec; i0 += 256 * UN) {
+          u32x4 av[UN], bv[VB][UN];
+#pragma unroll
+          for (int u = 0; u < UN; ++u) {
+            // lanes past the end load the chunk's first vector and drop it
+            const int i = i0 + 256 * u + tid;
+            const int64_t o = (int64_t)(i < nvec ? i : 0) * VE;
+            av[u] = ld16(a + o);
+#pragma unroll
+            for (int v = 0; v < VB; ++v)
+              if (v < nv) bv[v][u] = ld16(b[v] + o);
+          }
+#pragma unroll
+          for (int u = 0; u < UN; ++u)
+            if (i0 + 256 * u + tid < nvec)
+#pragma unroll
+              for (int v = 0; v < VB; ++v)
+                if (v < nv) add_vec<T>(acc[v], av[u], bv[v][u]);
+        }
+        done = nvec * VE;
+      }
+      for (int i = done + tid; i < len; i += 256)  // the remainder, or everything when a tensor is not 16-byte aligned
+#pragma unroll
+        for (int v = 0; v < VB; ++v)
+          if (v < nv) {
+            const double d = tod<T>(a[i]) - tod<T>(b[v][i]);
+            acc[v] = fma(d, d, acc[v]);
+          }
+#pragma unroll
+      for (int v = 0; v < VB; ++v) {
+        double s = sum16(acc[v]);
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lane == 0) red[wave][v] = s;
+      }
+      __syncthreads();
+      if (tid < nv)
+        st_agent(p.partials + (int64_t)(v0 + tid) * p.n_chunks + c,
+                 (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]));
+      __syncthreads();
+    }
+  }
+  // the last workgroup to get here sums everybody's partials
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's partials have reached memory
+  __syncthreads();
+  if (tid == 0)
+    is_last = __hip_atomic_fetch_add(p.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  __syncthreads();
+  if (!is_last) return;
+  // 16 lanes per output: sq[v, l] = sum of layer l's chunks, then per layer
+  // d_l = sqrt(sum_k sq[anchor(l), k]) (or of its own slice).  One workgroup is
+  // all latency here, so four outputs' loads go out before the first sum.
+  const int g = tid / 16, l16 = tid % 16, n_out = p.n_versions * p.n_layers;
+  for (int o0 = g; o0 < n_out; o0 += 64) {
+    double s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int o = o0 + 16 * j;
+      s[j] = 0.0;
+      if (o < n_out) {
+        const int v = o / p.n_layers, l = o % p.n_layers;
+        const double *q = p.partials + (int64_t)v * p.n_chunks;
+#pragma unroll 4
+        for (int c = p.first[l] + l16; c < p.first[l + 1]; c += 16) s[j] += ld_agent(q + c);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int o = o0 + 16 * j;
+      s[j] = sum16(s[j]);
+      if (l16 == 0 && o < n_out) {
+        if (o < SQ_LDS) sq_lds[o] = s[j];
+        st_agent(p.sq + o, s[j]);
+        if (p.sq_out) p.sq_out[o] = (float)s[j];
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int l = g; l < p.n_layers; l += 16) {
+    const int q0 = p.anchor[l] * p.n_layers;
+    double s = 0.0;
+    if (p.per_layer_only) {
+      s = q0 + l < SQ_LDS ? sq_lds[q0 + l] : ld_agent(p.sq + q0 + l);
+    } else {
+      for (int k = l16; k < p.n_layers; k += 16) s += q0 + k < SQ_LDS ? sq_lds[q0 + k] : ld_agent(p.sq + q0 + k);
+      s = sum16(s);
+    }
+    if (l16 == 0) {
+      const double d = sqrt(s);
+      p.drift[l] = (float)d;
+      p.risk[l] = (float)(d * (p.sens ? (double)p.sens[l] : 1.0));
+    }
   }
 }
 
+// Workgroups of a launch: 3 of 256 threads fit a CU.  28 layers of 7B shapes x 2
+// versions (242 MB): 256 -> 101 us a call, 512 -> 75, 768 -> 67, 1024 -> 73.
+constexpr int DRIFT_GRID = 768;
 constexpr int MAX_DEVICES = 64;
 void *g_scratch[MAX_DEVICES];
 std::once_flag g_scratch_once[MAX_DEVICES];
@@ -100,22 +220,14 @@ hipError_t drift_noalloc_scratch(void **out) {
   return g_scratch_err[dev];
 }
 
-hipError_t launch_drift_partials(hipStream_t s, const DriftSeg *segs, const DriftChunk *chunks, int n_chunks,
-                                 bool f32, double *partials) {
-  if (n_chunks <= 0) return hipSuccess;
+hipError_t launch_drift(hipStream_t s, bool f32, const DriftArgs &a) {
+  // at most DRIFT_GRID workgroups, each with every DRIFT_GRID-th chunk: the
+  // tickets are atomics on one address (no adapter at all: one, which writes zeros)
+  const dim3 grid(std::max(1, std::min(a.n_chunks, DRIFT_GRID)));
   if (f32)
-    hipLaunchKernelGGL(drift_partials_kernel<float>, dim3(n_chunks), dim3(256), 0, s, segs, chunks, partials);
+    hipLaunchKernelGGL(drift_kernel<float>, grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(drift_partials_kernel<bf16>, dim3(n_chunks), dim3(256), 0, s, segs, chunks, partials);
-  return hipGetLastError();
-}
-
-hipError_t launch_drift_finalize(hipStream_t s, const double *partials, const int *chunk_first,
-                                 const int *chunk_count, int n_versions, int n_layers, const int *anchor,
-                                 const float *sens, int per_layer_only, float *drift, float *risk, float *sq_out,
-                                 double *scratch) {
-  hipLaunchKernelGGL(drift_finalize_kernel, dim3(1), dim3(256), 0, s, partials, chunk_first, chunk_count,
-                     n_versions, n_layers, anchor, sens, per_layer_only, drift, risk, sq_out, scratch);
+    hipLaunchKernelGGL(drift_kernel<bf16>, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -160,24 +160,33 @@ hipError_t launch_attn_bf16(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf1
                             int nkv, int hd, float *part, int64_t part_floats);
 
 // ---------------------------------------------------------------- drift
+// One factor tensor of the current adapter; the same tensor of the stored
+// version v is b[seg * n_versions + v] of the launch.
 struct DriftSeg {
-  const void *a;     // current adapter tensor
-  const void *b;     // stored version tensor
+  const void *a;
   int64_t count;     // elements
-  int out;           // output index v * n_layers + l
 };
 struct DriftChunk {
-  int seg;
-  int64_t start, len;
+  int seg, idx;      // elements [idx * chunk, (idx + 1) * chunk) of the segment
 };
-hipError_t launch_drift_partials(hipStream_t s, const DriftSeg *segs, const DriftChunk *chunks, int n_chunks,
-                                 bool f32, double *partials);
+struct DriftArgs {
+  const DriftSeg *segs;
+  const void *const *b;
+  const DriftChunk *chunks;      // layer by layer
+  int n_chunks, chunk;           // chunk: elements, a multiple of 4096
+  const int *first;              // [n_layers + 1] first chunk of a layer
+  const int *anchor;             // [n_layers]
+  int n_versions, n_layers;
+  unsigned *ticket;              // zero at launch
+  double *partials;              // [n_versions][n_chunks]
+  double *sq;                    // [n_versions][n_layers] (workspace)
+  const float *sens;
+  int per_layer_only;
+  float *drift, *risk, *sq_out;  // sq_out nullable
+};
 // Device address of the no-allocation drift scratch on the current device
 // (CRF_DRIFT_NOALLOC_MAX_BYTES, looked up once per device).
 hipError_t drift_noalloc_scratch(void **out);
-hipError_t launch_drift_finalize(hipStream_t s, const double *partials, const int *chunk_first,
-                                 const int *chunk_count, int n_versions, int n_layers, const int *anchor,
-                                 const float *sens, int per_layer_only, float *drift, float *risk, float *sq_out,
-                                 double *scratch);
+hipError_t launch_drift(hipStream_t s, bool f32, const DriftArgs &a);
 
 }  // namespace crf
