@@ -128,7 +128,8 @@ int32_t crf_abi_version(void);
  * down-projections), a bf16 context holds fixed-size scratch for split
  * work: one 256x256 fp32 tile per compute unit for the K-parts of the QKV and
  * residual GEMMs (64 MiB on 256 CUs), key-split attention partials for
- * decoding steps (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats),
+ * decoding steps (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats, and
+ * at least 512 x 128 x (head_dim+4) when max_tokens >= 2048: 35 MB at most),
  * K-split LoRA partials and, when max_lora_rank > 0, the down projection's
  * adapter sums formed inside the gate/up projection (4 x 2 x 256 x 16 floats
  * per compute unit, 32 MiB on 256 CUs, plus one int per gate/up tile).  All of

@@ -806,6 +806,10 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
     if ((st = dmalloc(ctx, &ctx->proj16, 16 * (dq + 2 * dkv) * 4)) != CRF_OK) return cleanup(st);
     // key splits of >= 64 keys, up to 16 query rows per head, rows of hd + 4 floats
     ctx->attn_part_floats = (int64_t)((T + 63) / 64) * dims->n_q_heads * 16 * (dims->head_dim + 4);
+    // ... and for a prefix long enough to be split under whole query blocks, a
+    // block of 128 rows for each of 512 resident workgroups
+    if (T >= 2048)
+      ctx->attn_part_floats = std::max<int64_t>(ctx->attn_part_floats, (int64_t)512 * 128 * (dims->head_dim + 4));
     if ((st = dmalloc(ctx, &ctx->attn_part, (size_t)ctx->attn_part_floats * 4)) != CRF_OK) return cleanup(st);
     // K splits of >= 256 for up to 16 rows and three targets
     ctx->lora_part_floats = (int64_t)((std::max({D, f, dq}) + 255) / 256) * 16 * 3 * ctx->rank_pad;

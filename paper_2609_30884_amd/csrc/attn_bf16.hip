@@ -58,6 +58,7 @@ constexpr int BKV = 64;   // keys per tile
 constexpr float PSUM_MAX = 256.0f;  // bound on a half-block's probability sum (and each probability)
 constexpr int PGCAP = 2048;  // page bases staged in LDS at a time
 constexpr int SPLIT_WG = 1024;  // workgroups aimed at when a few query rows are split over the keys
+constexpr int ATTN_SLOTS = 512;  // resident workgroups of the GPU (two per CU)
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -135,12 +136,35 @@ inline int attn_window_grid(int nq, int nkv, int nqb, int &xcd_r) {
   return nqb * nq;
 }
 
+// Query head, query block and key split of workgroup `bid` of a key-split
+// launch; false for padding.  A unit is one split of one KV head: its workgroups
+// (every query block of the group's heads, or one when packed) read the same
+// K/V tiles, so they run on one XCD, units taking the XCDs in turn.
+__host__ __device__ inline bool attn_split_block(int bid, int nq, int nkv, int nqb, int n_splits, int packed,
+                                                 int &head, int &qblk, int &split) {
+  const int group = nq / nkv, per = packed ? 1 : group * nqb;
+  const int j = bid / 8, u = bid % 8 + 8 * (j / per), w = j % per;
+  if (u >= nkv * n_splits) return false;
+  split = u / nkv;
+  attn_block(packed ? u % nkv : 0, nq, nkv, nqb, 0, packed, head, qblk);
+  if (!packed) {
+    head = (u % nkv) * group + w / nqb;
+    qblk = nqb - 1 - w % nqb;
+  }
+  return true;
+}
+
+inline int attn_split_grid(int nq, int nkv, int nqb, int n_splits, int packed) {
+  return 8 * ((nkv * n_splits + 7) / 8) * (packed ? 1 : nq / nkv * nqb);
+}
+
 // PS: page size when fixed at compile time (16), 0 = runtime kv.page_size.
 template <int HD, int PS>
 __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__restrict__ Q, PagedKV kv,
                                                            bf16 *__restrict__ O, int Mq, int q_off, int nq,
                                                            int nkv, uint32_t pool_bytes, int xcd_r,
-                                                           int split_tiles, int packed, float *__restrict__ part) {
+                                                           int split_tiles, int n_splits, int packed,
+                                                           float *__restrict__ part) {
   constexpr int CH = HD / 8;             // 16-byte chunks per row
   constexpr int KS = HD / 16;            // MFMA k-steps for S
   constexpr int HB = HD / 32;            // 32-row hd blocks of O^T
@@ -159,8 +183,12 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
   const int M = q_off + Mq;  // keys
   const int nqb = (Mq + BQ - 1) / BQ;
   const int group = nq / nkv;
-  int head, qblk;
-  if (!attn_block(blockIdx.x, nq, nkv, nqb, xcd_r, packed, head, qblk)) return;
+  int head, qblk, split = 0;
+  if (split_tiles > 0) {
+    if (!attn_split_block(blockIdx.x, nq, nkv, nqb, n_splits, packed, head, qblk, split)) return;
+  } else if (!attn_block(blockIdx.x, nq, nkv, nqb, xcd_r, packed, head, qblk)) {
+    return;
+  }
   const int g_kv = head / group;
   const int ps = PS > 0 ? PS : kv.page_size;
   const int tid = threadIdx.x, lane = tid % 64;
@@ -193,11 +221,12 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
 
   const int last_key = min(q_off + q0 + BQ, M) - 1;
   const int ntiles = last_key / BKV + 1;
-  // Split over keys (a few query rows over a long prefix): this workgroup takes
-  // tiles [t_begin, t_end) and leaves an unnormalised partial for the merge.
+  // Split over keys (few query blocks over a long prefix): this workgroup takes
+  // tiles [t_begin, t_end) and leaves an unnormalised partial for the merge (of
+  // weight 0 where the range lies past every key of its rows).
   int t_begin = 0, t_end = ntiles;
   if (split_tiles > 0) {
-    t_begin = blockIdx.y * split_tiles;
+    t_begin = split * split_tiles;
     t_end = min(ntiles, t_begin + split_tiles);
   }
   const int n_pages_needed = last_key / ps + 1;
@@ -414,7 +443,7 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if (qi >= n_rows) return;
   if (split_tiles > 0) {  // partial: unnormalised O^T row, then the running max and sum
-    float *prow = part + (((int64_t)blockIdx.y * nq + qhead) * Mq + qrow) * (HD + 4);
+    float *prow = part + (((int64_t)split * nq + qhead) * Mq + qrow) * (HD + 4);
 #pragma unroll
     for (int b = 0; b < HB; ++b)
 #pragma unroll
@@ -501,18 +530,25 @@ void launch(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, in
     const int units = packed ? nkv : nq;
     split_tiles = std::max<int>(1, (ntiles * units + SPLIT_WG - 1) / SPLIT_WG);
     split_tiles = std::max<int>(split_tiles, (int)((ntiles + max_splits - 1) / max_splits));
+  } else if (nq * nqb * 2 <= ATTN_SLOTS && ntiles >= 32 && max_splits >= 2) {
+    // a few query blocks (the new tokens of a decoding step over a long prefix)
+    // leave most of the GPU idle: split the keys until every slot has a workgroup
+    int sp = std::min<int>(ATTN_SLOTS / (nq * nqb), (int)std::min<int64_t>(max_splits, ntiles / 8));
+    if (sp >= 2) split_tiles = (ntiles + sp - 1) / sp;
+  }
+  if (split_tiles > 0) {
     n_splits = (ntiles + split_tiles - 1) / split_tiles;
-    grid = units;
+    grid = attn_split_grid(nq, nkv, nqb, n_splits, packed);
   } else {
     grid = attn_window_grid(nq, nkv, nqb, xcd_r);
   }
-  const dim3 g3(grid, n_splits);
+  const dim3 g3(grid);
   if (kv.page_size == 16)
     hipLaunchKernelGGL((attn_bf16_kernel<HD, 16>), g3, dim3(NT), 0, s, Q, kv, O, Mq, q_off, nq, nkv, pool_bytes,
-                       xcd_r, split_tiles, packed, part);
+                       xcd_r, split_tiles, n_splits, packed, part);
   else
     hipLaunchKernelGGL((attn_bf16_kernel<HD, 0>), g3, dim3(NT), 0, s, Q, kv, O, Mq, q_off, nq, nkv, pool_bytes,
-                       xcd_r, split_tiles, packed, part);
+                       xcd_r, split_tiles, n_splits, packed, part);
   if (split_tiles > 0)
     hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(Mq * nq), dim3(256), 0, s, part, O, Mq, nq, n_splits);
 }
