@@ -19,7 +19,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcrf.so")
 ARCH = "gfx950"
 
-SOURCES = ["api.cpp", "norm.hip", "f32_path.hip", "lora_down.hip", "gemm_bf16.hip", "gemm_skinny.hip",
+SOURCES = ["api.cpp", "norm.hip", "f32_path.hip", "lora_down.hip", "gemm_bf16.hip", "gemm_skinny.hip", "gemm_mid.hip",
            "attn_bf16.hip", "drift.hip"]
 
 CFLAGS = [

@@ -284,6 +284,157 @@ bool has_lora(const crf_lora_layer *lora, int l, int t) {
   return lora && lora[l].rank > 0 && lora[l].A[t] != nullptr;
 }
 
+// The same layers for token counts between the weight-streaming kernels' and
+// the large tiles' (gemm_mid.hip).
+crf_status run_layers_mid(crf_context *ctx, const void *hb, const crf_layer_weights *W, const crf_lora_layer *lora,
+                          int l0, int h, const crf_kv_cache *kv, void *hout, hipStream_t s, int rows, int pos0,
+                          bool kv_tail) {
+  const crf_model_dims &d = ctx->dims;
+  const int M = rows, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
+  const int rp = ctx->rank_pad, ldu = 3 * rp;
+  bf16 *xn = (bf16 *)ctx->xn, *q = (bf16 *)ctx->q, *attn = (bf16 *)ctx->attn, *act = (bf16 *)ctx->act;
+  bf16 *u = (bf16 *)ctx->u;
+  LAUNCH(ctx, s, CRF_KK_NORM, launch_rmsnorm(s, hb, false, W[l0].attn_norm, xn, nullptr, M, D, d.rms_eps));
+  for (int l = l0; l < l0 + h; ++l) {
+    const crf_layer_weights &w = W[l];
+    const bool last = l == l0 + h - 1, kv_only = last && !hout && kv_tail;
+    const int rank = lora ? lora[l].rank : 0;
+    // x W^T of targets t0 .. t0 + n - 1 with their adapters' A rows behind
+    auto product = [&](const bf16 *x, int K, int t0, int n, MidReduce &r, int kind) -> crf_status {
+      MidGemm p{};
+      p.X = x;
+      p.ldx = K;
+      p.M = M;
+      p.K = K;
+      int seg = 0;
+      auto add = [&](const void *ptr, int n_rows) {
+        p.w[seg] = (const bf16 *)ptr;
+        p.w_rows[seg] = n_rows;
+        p.N += n_rows;
+        p.seg_end[seg++] = p.N;
+      };
+      for (int i = 0; i < n; ++i) {
+        int d_out, d_in;
+        target_shape(d, t0 + i, d_out, d_in);
+        add(w.w[t0 + i], d_out);
+      }
+      r = MidReduce{};
+      r.n_base = p.N;
+      for (int i = 0; i < n; ++i) {
+        if (!has_lora(lora, l, t0 + i)) continue;
+        r.ucol[i] = p.N - r.n_base;
+        r.lb[i] = (const bf16 *)lora[l].B[t0 + i];
+        add(lora[l].A[t0 + i], rank);
+      }
+      for (; seg < MID_SEGS; ++seg) p.seg_end[seg] = p.N;
+      r.n_u = p.N - r.n_base;
+      r.ld = p.N;
+      r.M = M;
+      r.rank = rank;
+      r.scale = lora ? lora[l].scale : 0.f;
+      r.part = p.part = ctx->gemm_part;
+      // (K and V alone are summed in the same parts as with Q next to them: the
+      // cache is the same to the bit)
+      const int n_split = t0 + n == CRF_O ? dq + 2 * dkv + 3 * rank : p.N;
+      r.parts = p.parts = mid_parts(M, n_split, K, ctx->n_cu, ctx->gemm_part_floats);
+      LAUNCH(ctx, s, kind, launch_gemm_mid(s, false, p));
+      return CRF_OK;
+    };
+    crf_status st;
+    MidReduce r;
+    {
+      const int t0 = kv_only ? CRF_K : CRF_Q;
+      if ((st = product(xn, D, t0, CRF_O - t0, r, CRF_KK_GEMM_QKV)) != CRF_OK) return st;
+      if (kv_only) {  // no query rows: segments 1 and 2 only
+        for (int i = 2; i > 0; --i) {
+          r.lb[i] = r.lb[i - 1];
+          r.ucol[i] = r.ucol[i - 1];
+        }
+        r.lb[0] = nullptr;
+      }
+      r.seg1 = kv_only ? 0 : dq;
+      r.seg2 = r.seg1 + dkv;
+      r.hd = hd;
+      r.dq = dq;
+      r.pos0 = pos0;
+      r.q_scale = attn_query_scale(hd);
+      r.bias[0] = (const bf16 *)w.bias_q;
+      r.bias[1] = (const bf16 *)w.bias_k;
+      r.bias[2] = (const bf16 *)w.bias_v;
+      r.q_out = q;
+      r.kv = layer_kv(ctx, kv, l);
+      r.rope_cs = ctx->rope_cs;
+      LAUNCH(ctx, s, CRF_KK_GEMM_QKV, launch_mid_reduce_qkv(s, r));
+    }
+    if (kv_only) break;  // nothing reads this layer's output
+    LAUNCH(ctx, s, CRF_KK_ATTN,
+           launch_attn_bf16(s, q, layer_kv(ctx, kv, l), attn, M, pos0, d.n_q_heads, d.n_kv_heads, hd, ctx->attn_part,
+                            ctx->attn_part_floats));
+    {
+      if ((st = product(attn, dq, CRF_O, 1, r, CRF_KK_GEMM_O)) != CRF_OK) return st;
+      r.resid = ctx->hres;
+      r.resid_in = l == l0 ? (const bf16 *)hb : nullptr;
+      r.gain = (const bf16 *)w.mlp_norm;
+      r.eps = d.rms_eps;
+      r.xn = xn;
+      LAUNCH(ctx, s, CRF_KK_GEMM_O, launch_mid_reduce_resid(s, r));
+    }
+    {
+      MidGemm p{};
+      p.X = xn;
+      p.ldx = D;
+      p.M = M;
+      p.K = D;
+      p.N = 2 * f;
+      p.parts = 1;
+      p.act = act;
+      p.d_ffn = f;
+      p.rank = rank;
+      p.ldu = ldu;
+      LoraDownTarget tg[2];
+      for (int i = 0; i < 2; ++i) {
+        const int t = CRF_GATE + i;
+        const bool on = has_lora(lora, l, t);
+        tg[i] = LoraDownTarget{on ? (const bf16 *)lora[l].A[t] : nullptr, rank, lora ? lora[l].scale : 0.f, i * rp};
+        p.w[i] = (const bf16 *)w.w[t];
+        p.w_rows[i] = f;
+        p.lb[i] = on ? (const bf16 *)lora[l].B[t] : nullptr;
+        p.ucol[i] = i * rp;
+        if (on) p.U = u;
+      }
+      if (p.U)
+        LAUNCH(ctx, s, CRF_KK_LORA_DOWN,
+               launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats));
+      LAUNCH(ctx, s, CRF_KK_GEMM_GATEUP, launch_gemm_mid(s, true, p));
+    }
+    {
+      if ((st = product(act, f, CRF_DOWN, 1, r, CRF_KK_GEMM_DOWN)) != CRF_OK) return st;
+      r.resid = ctx->hres;
+      r.resid_out = last ? (bf16 *)hout : nullptr;
+      if (!last) {
+        r.gain = (const bf16 *)W[l + 1].attn_norm;
+        r.eps = d.rms_eps;
+        r.xn = xn;
+      }
+      LAUNCH(ctx, s, CRF_KK_GEMM_DOWN, launch_mid_reduce_resid(s, r));
+    }
+  }
+  return CRF_OK;
+}
+
+// Whether a run of `rows` token rows takes the kernels above: while its gate/up
+// projection has at most two rounds of 256x256 tiles, with whole rounds of which
+// the large tiles win (two layers of 1.5B shapes: 1600 tokens 534 against 576
+// us, 2048 tokens 778 against 769; of 7B shapes: 700 tokens 1025 against 1020,
+// 1024 tokens 1320 against 1273).
+bool mid_rows(const crf_context *ctx, int rows) {
+  const crf_model_dims &d = ctx->dims;
+  if (rows <= 16 || d.d_model > MID_MAX_COLS || ctx->n_cu <= 0) return false;
+  const int64_t tiles = (int64_t)((rows + 255) / 256) * ((2 * d.d_ffn + 255) / 256);
+  const int64_t cols = std::max<int64_t>(dq_of(d) + 2 * dkv_of(d), d.d_model) + 3 * ctx->max_rank;
+  return tiles <= 2 * ctx->n_cu && rows * cols <= ctx->gemm_part_floats;
+}
+
 // Layers [l0, l0+h) over `rows` token rows at positions pos0..pos0+rows-1: a
 // window (pos0 = 0, rows = the prefix) or new tokens over a cached prefix
 // (pos0 = the prefix length).  kv_tail: without hidden_out the last layer runs
@@ -291,6 +442,7 @@ bool has_lora(const crf_lora_layer *lora, int l, int t) {
 crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_weights *W,
                            const crf_lora_layer *lora, int l0, int h, const crf_kv_cache *kv, void *hout,
                            hipStream_t s, int rows, int pos0, bool kv_tail) {
+  if (mid_rows(ctx, rows)) return run_layers_mid(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
   const crf_model_dims &d = ctx->dims;
   const int M = rows, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
   const int rp = ctx->rank_pad, ldu = 3 * rp;

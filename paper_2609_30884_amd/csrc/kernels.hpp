@@ -149,6 +149,58 @@ hipError_t launch_gemm_dn_sum(hipStream_t s, const GemmParams &p, bf16 *U, int l
 // The same projections for M <= 16 token rows (weight-streaming bound).
 hipError_t launch_gemm_skinny_bf16(hipStream_t s, GemmEpi epi, int hd, const GemmParams &p);
 
+// ---- 17 to MID_MAX_ROWS token rows (gemm_mid.hip)
+constexpr int MID_SEGS = 6;       // row sources of a launch: up to three weights, then their A factors
+constexpr int MID_MAX_COLS = 8192;  // widest residual row of reduce_resid
+// Y = X W^T over the concatenated rows [0, N) of the segments (each a multiple
+// of 8 rows): fp32 K-parts part[s][m][n], s < parts; or for gate/up (segments 0
+// and 1 in tile space, N = 2 d_ffn, parts = 1) act = silu(gate) * up.
+struct MidGemm {
+  const bf16 *X;
+  int64_t ldx;
+  int M, K, N;
+  const bf16 *w[MID_SEGS];
+  int w_rows[MID_SEGS], seg_end[MID_SEGS];  // rows of a segment; first row after it
+  int parts, tiles_m;  // tiles_m is set by the launcher
+  float *part;
+  // gate/up: adapter delta U lb^T and the output
+  const bf16 *U;
+  int ldu, rank, ucol[2];
+  const bf16 *lb[2];
+  bf16 *act;
+  int d_ffn;
+};
+// K-parts that fill the GPU for a product of N rows, within part_floats floats
+int mid_parts(int M, int N, int K, int n_cu, int64_t part_floats);
+hipError_t launch_gemm_mid(hipStream_t s, bool gate_up, const MidGemm &p);
+// Sums the parts of [M, ld] (n_base base columns, then n_u adapter columns) and
+// finishes the projection of each token (see gemm_mid.hip).
+struct MidReduce {
+  const float *part;
+  int parts, M, ld, n_base, n_u;
+  float scale;             // of the adapter
+  int rank, ucol[3];       // columns of the targets' U among the n_u
+  const bf16 *lb[3];       // [rows, rank] or null
+  // QKV: segments [0, seg1) Q, [seg1, seg2) K, [seg2, n_base) V
+  int seg1, seg2, hd, dq, pos0;
+  float q_scale;
+  const bf16 *bias[3];
+  bf16 *q_out;
+  PagedKV kv;
+  const float2 *rope_cs;
+  // residual rows: resid (fp32) += sum, the old value from resid_in when given;
+  // resid_out (nullable) takes the result in bf16 instead; with a gain, xn =
+  // RMSNorm of the result
+  float *resid;
+  const bf16 *resid_in;
+  bf16 *resid_out;
+  const bf16 *gain;
+  float eps;
+  bf16 *xn;
+};
+hipError_t launch_mid_reduce_qkv(hipStream_t s, const MidReduce &p);
+hipError_t launch_mid_reduce_resid(hipStream_t s, const MidReduce &p);
+
 // Factor the attention kernel expects the stored query rows to carry:
 // log2(e) / sqrt(head_dim) (scores then come out in log2 units).
 inline float attn_query_scale(int hd) { return 1.4426950408889634f / __builtin_sqrtf((float)hd); }
