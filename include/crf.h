@@ -132,7 +132,8 @@ int32_t crf_abi_version(void);
  * at least 512 x 128 x (head_dim+4) when max_tokens >= 2048: 35 MB at most),
  * K-split LoRA partials and, when max_lora_rank > 0, the down projection's
  * adapter sums formed inside the gate/up projection (4 x 2 x 256 x 16 floats
- * per compute unit, 32 MiB on 256 CUs, plus one int per gate/up tile).  All of
+ * per compute unit, 32 MiB on 256 CUs, plus one int per gate/up tile), and 2 KiB
+ * of arrival counters.  All of
  * it is freed by crf_context_destroy.  On success *out
  * receives the context.  Errors: INVALID_ARG (null), UNSUPPORTED (see
  * crf_validate_dims), HIP (allocation failed). */

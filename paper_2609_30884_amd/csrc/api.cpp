@@ -62,6 +62,8 @@ struct crf_context {
   int64_t gemm_part_floats = 0;
   float *dn_part = nullptr;    // bf16 path: down-projection adapter sums fused into gate/up
   int *dn_head = nullptr;      //   and the table of their first tiles
+  unsigned *tickets = nullptr; // bf16 path: arrival counters of K-split workgroups, zero between launches
+  int n_tickets = 0;
   int n_cu = 0;
   // drift staging
   DriftStage drift_stage[4];
@@ -280,6 +282,11 @@ PagedKV layer_kv(crf_context *ctx, const crf_kv_cache *kv, int l) {
   return p;
 }
 
+// (the K-part buffer of the projections is free while a LoRA down-projection runs)
+LoraWs lora_ws(const crf_context *ctx) {
+  return LoraWs{ctx->gemm_part, ctx->gemm_part_floats, ctx->tickets, ctx->n_tickets};
+}
+
 bool has_lora(const crf_lora_layer *lora, int l, int t) {
   return lora && lora[l].rank > 0 && lora[l].A[t] != nullptr;
 }
@@ -404,7 +411,8 @@ crf_status run_layers_mid(crf_context *ctx, const void *hb, const crf_layer_weig
       }
       if (p.U)
         LAUNCH(ctx, s, CRF_KK_LORA_DOWN,
-               launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats));
+               launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, nullptr,
+                                     lora_ws(ctx)));
       LAUNCH(ctx, s, CRF_KK_GEMM_GATEUP, launch_gemm_mid(s, true, p));
     }
     {
@@ -510,7 +518,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       // Nothing reads this layer's output: its cache entry depends only on its
       // input through the K and V projections, so only those run.
       const bool kv_any = lora_targets({CRF_K, CRF_V}, tg);
-      if (kv_any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit));
+      if (kv_any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
       GemmParams p = base_params(xn, D, 2 * dkv);
       p.w[1] = (const bf16 *)w.w[CRF_K];
       p.w[2] = (const bf16 *)w.w[CRF_V];
@@ -532,7 +540,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       break;
     }
     bool any = lora_targets({CRF_Q, CRF_K, CRF_V}, tg);
-    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 3, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit));
+    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 3, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
     {
       GemmParams p = base_params(xn, D, dq + 2 * dkv);
       p.w[0] = (const bf16 *)w.w[CRF_Q];
@@ -560,7 +568,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
            launch_attn_bf16(s, q, layer_kv(ctx, kv, l), attn, M, pos0, d.n_q_heads, d.n_kv_heads, hd,
                             ctx->attn_part, ctx->attn_part_floats));
     any = lora_targets({CRF_O}, tg);
-    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, attn, dq, M, dq, tg, 1, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit));
+    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, attn, dq, M, dq, tg, 1, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
     {
       GemmParams p = base_params(attn, dq, D);
       p.w[0] = (const bf16 *)w.w[CRF_O];
@@ -578,7 +586,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
     LAUNCH(ctx, s, CRF_KK_NORM,
            launch_rmsnorm(s, ctx->hres, true, w.mlp_norm, xn, nullptr, M, D, d.rms_eps));
     any = lora_targets({CRF_GATE, CRF_UP}, tg);
-    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit));
+    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
     // the down projection's adapter down-projection rides on the gate/up
     // epilogue when its rank fits (dn_done), else it is a pass of its own
     bool dn_done = false;
@@ -609,7 +617,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
     if (any && dn_done)
       LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_gemm_dn_sum(s, pgu, u, ldu, 0, scale));
     else if (any)
-      LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, act, f, M, f, tg, 1, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit));
+      LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, act, f, M, f, tg, 1, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
     {
       GemmParams p = base_params(act, f, D);
       p.w[0] = (const bf16 *)w.w[CRF_DOWN];
@@ -907,7 +915,7 @@ void crf_context_destroy(crf_context *ctx) {
   if (!ctx) return;
   void *bufs[] = {ctx->hres, ctx->xn, ctx->q, ctx->attn, ctx->act, ctx->u, ctx->rope_cs,
                   ctx->d_err, ctx->drift_dev, ctx->proj16, ctx->attn_part, ctx->lora_part, ctx->gemm_part,
-                  ctx->dn_part, ctx->dn_head};
+                  ctx->dn_part, ctx->dn_head, ctx->tickets};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   for (DriftStage &st : ctx->drift_stage) {
@@ -970,6 +978,10 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
     if (hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
       ctx->n_cu = 0;
     ctx->gemm_part_floats = (int64_t)std::max(ctx->n_cu, 0) * 256 * 256;
+    ctx->n_tickets = 512;
+    if ((st = dmalloc(ctx, &ctx->tickets, ctx->n_tickets * sizeof(unsigned))) != CRF_OK) return cleanup(st);
+    if (hipMemset(ctx->tickets, 0, ctx->n_tickets * sizeof(unsigned)) != hipSuccess)
+      return cleanup(fail(ctx, CRF_ERR_HIP, "context init: hipMemset"));
     if (ctx->gemm_part_floats > 0 &&
         (st = dmalloc(ctx, &ctx->gemm_part, (size_t)ctx->gemm_part_floats * 4)) != CRF_OK)
       return cleanup(st);

@@ -67,6 +67,26 @@ CRF_DEV void dma16(__amdgpu_buffer_rsrc_t r, lds_char *lds, uint32_t voff, uint3
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)lds, 16, voff, soff, 0, 0);
 }
 
+// Values that workgroups hand to each other inside a launch: agent-scope
+// accesses go to memory, past the XCDs' L2 caches, which are not coherent with
+// each other.  The writer waits for its stores (agent_flush) before it takes a
+// ticket; whoever draws the last ticket may read them.
+CRF_DEV void st_agent16(float *p, f32x4 v) {
+  const u32x4 u = __builtin_bit_cast(u32x4, v);
+  __hip_atomic_store((uint64_t *)p, (uint64_t)u[0] | (uint64_t)u[1] << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store((uint64_t *)p + 1, (uint64_t)u[2] | (uint64_t)u[3] << 32, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+CRF_DEV f32x4 ld_agent16(const float *p) {
+  const uint64_t a = __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t b = __hip_atomic_load((const uint64_t *)p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __builtin_bit_cast(f32x4, u32x4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)});
+}
+CRF_DEV void agent_flush() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+CRF_DEV unsigned agent_ticket(unsigned *t) {
+  return __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 CRF_DEV float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);

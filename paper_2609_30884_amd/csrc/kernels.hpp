@@ -71,9 +71,17 @@ struct LoraSplit {
   int n_parts = 0;
   int cols = 0;
 };
+// For M > 16, workspace to split K over workgroups: `floats` floats, and
+// n_tickets counters that are zero between launches.
+struct LoraWs {
+  float *blocks = nullptr;
+  int64_t floats = 0;
+  unsigned *tickets = nullptr;
+  int n_tickets = 0;
+};
 hipError_t launch_lora_down_bf16(hipStream_t s, const bf16 *X, int64_t ldx, int M, int K, const LoraDownTarget *t,
                                  int n_targets, int rank_pad, bf16 *U, int ldu, float *ws, int64_t ws_floats,
-                                 LoraSplit *split = nullptr);
+                                 LoraSplit *split, const LoraWs &lw);
 
 enum GemmEpi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
 

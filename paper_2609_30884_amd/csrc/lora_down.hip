@@ -1,6 +1,8 @@
 // Skinny LoRA down-projection U = scale * X A^T for up to three adapter targets
 // that read the same input (q/k/v, gate/up, o or down).  The input is read
 // once; the r x K factors stay in L2.  HBM-bound.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace crf {
@@ -23,6 +25,11 @@ struct LdArgs {
   int ldu;
   int spw;      // k-steps of 32 per workgroup along grid.y
   float *part;  // non-null: fp32 partial sums [grid.y][16][n_targets * rank_pad], unscaled
+  // non-null: K split over grid.y workgroups, whose partial blocks go to
+  // `blocks` [token block][grid.y][NB][64][4] and are summed by the last of
+  // them; one ticket per token block, zero between launches
+  unsigned *tickets;
+  float *blocks;
 };
 
 // Workgroup: TB blocks of 16 tokens, NW waves splitting K (wave w takes k-steps
@@ -91,15 +98,17 @@ __global__ __launch_bounds__(64 * NW) void lora_down_kernel(LdArgs a) {
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) red[wave][b * TB + tb][lane] = acc[b][tb];
   __syncthreads();
-  // wave w finishes token block w (TB <= 4)
-  if (wave >= TB) return;
-  const int m = m0 + 16 * wave + lane % 16;
-  if (m >= a.M) return;
+  // the waves share the blocks' final sums
+  for (int i = wave; i < NB * TB; i += NW) {
+    const int b = i / TB, tb = i % TB, m = m0 + 16 * tb + lane % 16;
+    f32x4 v = red[0][i][lane];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    f32x4 v = red[0][b * TB + wave][lane];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) v += red[w][b * TB + wave][lane];
+    for (int w = 1; w < NW; ++w) v += red[w][i][lane];
+    if (a.tickets) {
+      st_agent16(a.blocks + ((((int64_t)blockIdx.x * gridDim.y + blockIdx.y) * NB + b) * 64 + lane) * 4, v);
+      continue;
+    }
+    if (m >= a.M) continue;
     if (a.part) {  // K split over workgroups: unscaled partial, summed by lora_down_sum_kernel
       const int ncols = a.n_targets * a.rank_pad;
       *reinterpret_cast<f32x4 *>(a.part + ((int64_t)blockIdx.y * 16 + m) * ncols + b * 16 + (lane / 16) * 4) = v;
@@ -107,6 +116,34 @@ __global__ __launch_bounds__(64 * NW) void lora_down_kernel(LdArgs a) {
     }
     const int t = (b * 16) / a.rank_pad;
     const int jb = b * 16 - t * a.rank_pad + (lane / 16) * 4;  // first of 4 rows held by this lane
+    const float sc = a.scale[t];
+    st8(a.U + (int64_t)m * a.ldu + a.ucol[t] + jb, pack_bf16x4(v[0] * sc, v[1] * sc, v[2] * sc, v[3] * sc));
+  }
+  if (TB > 1 || !a.tickets) return;
+  __shared__ bool is_last;
+  agent_flush();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    is_last = agent_ticket(a.tickets + blockIdx.x) == gridDim.y - 1;
+    if (is_last) __hip_atomic_store(a.tickets + blockIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (!is_last) return;
+  for (int b = wave; b < NB; b += NW) {
+    const float *q = a.blocks + (((int64_t)blockIdx.x * gridDim.y * NB + b) * 64 + lane) * 4;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    for (int y0 = 0; y0 < (int)gridDim.y; y0 += 4) {
+      f32x4 t[4];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) t[y] = ld_agent16(q + (int64_t)min(y0 + y, (int)gridDim.y - 1) * NB * 256);
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+        if (y0 + y < (int)gridDim.y) v += t[y];
+    }
+    const int m = m0 + lane % 16;
+    if (m >= a.M) continue;
+    const int t = (b * 16) / a.rank_pad;
+    const int jb = b * 16 - t * a.rank_pad + (lane / 16) * 4;
     const float sc = a.scale[t];
     st8(a.U + (int64_t)m * a.ldu + a.ucol[t] + jb, pack_bf16x4(v[0] * sc, v[1] * sc, v[2] * sc, v[3] * sc));
   }
@@ -132,7 +169,7 @@ __global__ __launch_bounds__(256) void lora_down_sum_kernel(LdArgs a, int n_spli
 }
 
 template <int NB>
-void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *split) {
+void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *few, const LoraWs &lw) {
   constexpr int UNROLL = NB <= 4 ? 8 : 2;
   const int nsteps = a.K / 32;
   // a few token rows: split K over workgroups (one batch of loads per wave)
@@ -142,9 +179,9 @@ void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *split)
     a.spw = spw;
     a.part = ws;
     hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(1, n_split), dim3(256), 0, s, a);
-    if (split && n_split <= 4) {  // the consumer sums the partials
-      split->n_parts = n_split;
-      split->cols = a.n_targets * a.rank_pad;
+    if (few && n_split <= 4) {  // the consumer sums the partials
+      few->n_parts = n_split;
+      few->cols = a.n_targets * a.rank_pad;
       return;
     }
     hipLaunchKernelGGL(lora_down_sum_kernel, dim3((a.M * a.n_targets * a.rank_pad + 15) / 16), dim3(256), 0, s, a,
@@ -161,14 +198,30 @@ void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *split)
       return;
     }
   }
-  hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3((a.M + 15) / 16), dim3(256), 0, s, a);
+  // Fewer tokens: 16 per workgroup.  A workgroup is bound by what one CU can
+  // read (its tokens and all of the factors), so K is split over workgroups
+  // until there are about two to a CU, of at least 16 k-steps.  777 tokens of 7B
+  // shapes, rank 32: down (K = 18944) 85 -> 19 us, o (K = 3584) 22 -> 8, gate/up
+  // 22 -> 12.  Two parts of 256 token blocks are slower than none (4096 tokens of
+  // 1.5B shapes, q/k/v: 12.4 against 11.2 us).
+  const int mb = (a.M + 15) / 16;
+  const int64_t cap = lw.blocks ? lw.floats / ((int64_t)mb * NB * 256) : 0;
+  const int64_t split = std::min<int64_t>({512 / mb, nsteps / 16, cap, 64});
+  if (split >= 3 && lw.tickets && mb <= lw.n_tickets) {
+    a.spw = (int)((nsteps + split - 1) / split);
+    a.tickets = lw.tickets;
+    a.blocks = lw.blocks;
+    hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(mb, (nsteps + a.spw - 1) / a.spw), dim3(256), 0, s, a);
+    return;
+  }
+  hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(mb), dim3(256), 0, s, a);
 }
 
 }  // namespace
 
 hipError_t launch_lora_down_bf16(hipStream_t s, const bf16 *X, int64_t ldx, int M, int K, const LoraDownTarget *t,
                                  int n_targets, int rank_pad, bf16 *U, int ldu, float *ws, int64_t ws_floats,
-                                 LoraSplit *split) {
+                                 LoraSplit *split, const LoraWs &lw) {
   if (split) *split = LoraSplit{};
   if (M <= 0 || n_targets <= 0) return hipSuccess;
   if (n_targets > MAXT || n_targets * rank_pad > MAXB * 16 || rank_pad % 16 || K % 32) return hipErrorInvalidValue;
@@ -188,14 +241,14 @@ hipError_t launch_lora_down_bf16(hipStream_t s, const bf16 *X, int64_t ldx, int 
   a.U = U;
   a.ldu = ldu;
   switch (n_targets * rank_pad / 16) {
-    case 1: go<1>(s, a, ws, ws_floats, split); break;
-    case 2: go<2>(s, a, ws, ws_floats, split); break;
-    case 3: go<3>(s, a, ws, ws_floats, split); break;
-    case 4: go<4>(s, a, ws, ws_floats, split); break;
-    case 6: go<6>(s, a, ws, ws_floats, split); break;
-    case 8: go<8>(s, a, ws, ws_floats, split); break;
-    case 9: go<9>(s, a, ws, ws_floats, split); break;
-    case 12: go<12>(s, a, ws, ws_floats, split); break;
+    case 1: go<1>(s, a, ws, ws_floats, split, lw); break;
+    case 2: go<2>(s, a, ws, ws_floats, split, lw); break;
+    case 3: go<3>(s, a, ws, ws_floats, split, lw); break;
+    case 4: go<4>(s, a, ws, ws_floats, split, lw); break;
+    case 6: go<6>(s, a, ws, ws_floats, split, lw); break;
+    case 8: go<8>(s, a, ws, ws_floats, split, lw); break;
+    case 9: go<9>(s, a, ws, ws_floats, split, lw); break;
+    case 12: go<12>(s, a, ws, ws_floats, split, lw); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
