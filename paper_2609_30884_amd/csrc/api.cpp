@@ -53,10 +53,9 @@ struct crf_context {
   void *u = nullptr;       // bf16: [T, 3*rank_pad] LoRA down-projections; fp32: [T, 3*max_rank] past the fused ranks
   float2 *rope_cs = nullptr;
   int *d_err = nullptr;
-  float *proj16 = nullptr;  // bf16 path, <= 16 token rows: fp32 Q/K/V projections [16, dq + 2 dkv]
   float *attn_part = nullptr;  // bf16 path, <= 16 query rows: key-split attention partials
   int64_t attn_part_floats = 0;
-  float *lora_part = nullptr;  // bf16 path, <= 16 token rows: K-split LoRA down-projection partials
+  float *lora_part = nullptr;  // bf16 path, <= 16 token rows: parts of the LoRA down-projections
   int64_t lora_part_floats = 0;
   float *gemm_part = nullptr;  // bf16 path: K-part partials of the last residual GEMM tiles
   int64_t gemm_part_floats = 0;
@@ -411,8 +410,7 @@ crf_status run_layers_mid(crf_context *ctx, const void *hb, const crf_layer_weig
       }
       if (p.U)
         LAUNCH(ctx, s, CRF_KK_LORA_DOWN,
-               launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, nullptr,
-                                     lora_ws(ctx)));
+               launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, nullptr, 0, nullptr, lora_ws(ctx)));
       LAUNCH(ctx, s, CRF_KK_GEMM_GATEUP, launch_gemm_mid(s, true, p));
     }
     {
@@ -443,6 +441,130 @@ bool mid_rows(const crf_context *ctx, int rows) {
   return tiles <= 2 * ctx->n_cu && rows * cols <= ctx->gemm_part_floats;
 }
 
+// The same layers for up to 16 token rows (the new tokens of a decoding step, a
+// very short window): weight-streaming projections, each fed the adapter's U as
+// parts by the launch before it.
+crf_status run_layers_few(crf_context *ctx, const void *hb, const crf_layer_weights *W, const crf_lora_layer *lora,
+                          int l0, int h, const crf_kv_cache *kv, void *hout, hipStream_t s, int rows, int pos0,
+                          bool kv_tail) {
+  const crf_model_dims &d = ctx->dims;
+  const int M = rows, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
+  const int rp = ctx->rank_pad;
+  bf16 *xn = (bf16 *)ctx->xn, *q = (bf16 *)ctx->q, *attn = (bf16 *)ctx->attn, *act = (bf16 *)ctx->act;
+  for (int l = l0; l < l0 + h; ++l) {
+    const crf_layer_weights &w = W[l];
+    const bool first = l == l0, last = l == l0 + h - 1, kv_only = last && !hout && kv_tail;
+    const int rank = lora ? lora[l].rank : 0;
+    auto params = [&](const bf16 *X, int K, int N) {
+      GemmParams p{};
+      p.X = X;
+      p.ldx = K;
+      p.M = M;
+      p.K = K;
+      p.N = N;
+      p.rank = rank;
+      p.uscale = lora ? lora[l].scale : 0.f;
+      p.upart = ctx->lora_part;
+      p.rope_cs = ctx->rope_cs;
+      p.q_scale = attn_query_scale(hd);
+      p.pos0 = pos0;
+      p.n_cu = ctx->n_cu;
+      p.split_part = ctx->gemm_part;
+      p.split_cap = ctx->gemm_part_floats;
+      p.tickets = ctx->tickets;
+      p.n_tickets = ctx->n_tickets;
+      p.hd = hd;
+      p.resid = ctx->hres;
+      p.ldr = D;
+      return p;
+    };
+    // xn = RMSNorm of the residual stream, with the parts of U for targets
+    // t0 .. t0 + n - 1 (segments s0, ... of p)
+    auto norm = [&](const void *gain, bool boundary, int t0, int n, int s0, GemmParams &p) {
+      NormLora nl{};
+      nl.x = boundary ? hb : (const void *)ctx->hres;
+      nl.g = (const bf16 *)gain;
+      nl.y = xn;
+      nl.copy_out = boundary ? ctx->hres : nullptr;
+      nl.M = M;
+      nl.d = D;
+      nl.eps = d.rms_eps;
+      nl.rank = rank;
+      nl.rank_pad = rp;
+      nl.part = ctx->lora_part;
+      bool any = false;
+      for (int i = 0; i < n; ++i) {
+        if (!has_lora(lora, l, t0 + i)) continue;
+        any = true;
+        nl.A[i] = (const bf16 *)lora[l].A[t0 + i];
+        p.lb[s0 + i] = (const bf16 *)lora[l].B[t0 + i];
+        p.ucol[s0 + i] = i * rp;
+      }
+      p.upart_n = any ? norm_lora_parts(D) : 0;
+      p.upart_cols = n * rp;
+      return launch_norm_lora(s, !boundary, nl, any ? n * rp / 16 : 0);
+    };
+    // the parts of U of one target over K = d_in
+    auto lora_down = [&](const bf16 *X, int K, int t, GemmParams &p) {
+      const LoraDownTarget tg{(const bf16 *)lora[l].A[t], rank, lora[l].scale, 0};
+      p.lb[0] = (const bf16 *)lora[l].B[t];
+      p.upart_cols = rp;
+      return launch_lora_down_bf16(s, X, K, M, K, &tg, 1, rp, nullptr, 0, ctx->lora_part, ctx->lora_part_floats,
+                                   &p.upart_n, LoraWs{});
+    };
+    {
+      GemmParams p = params(xn, D, (kv_only ? 0 : dq) + 2 * dkv);
+      const int s0 = kv_only ? 1 : 0;  // no query rows: K and V only
+      for (int i = s0; i < 3; ++i) p.w[i] = (const bf16 *)w.w[CRF_Q + i];
+      p.seg1 = kv_only ? 0 : dq;
+      p.seg2 = p.seg1 + dkv;
+      p.bias[0] = (const bf16 *)w.bias_q;
+      p.bias[1] = (const bf16 *)w.bias_k;
+      p.bias[2] = (const bf16 *)w.bias_v;
+      p.q_out = q;
+      p.dq = dq;
+      p.kv = layer_kv(ctx, kv, l);
+      LAUNCH(ctx, s, CRF_KK_NORM, norm(w.attn_norm, first, CRF_Q + s0, 3 - s0, s0, p));
+      LAUNCH(ctx, s, CRF_KK_GEMM_QKV, launch_gemm_skinny_bf16(s, EPI_QKV, p));
+    }
+    if (kv_only) break;  // nothing reads this layer's output
+    {
+      GemmParams p = params(attn, dq, D);
+      const bool lo = has_lora(lora, l, CRF_O);
+      AttnLora al{lo ? (const bf16 *)lora[l].A[CRF_O] : nullptr, rank, rp, ctx->lora_part, 0};
+      LAUNCH(ctx, s, CRF_KK_ATTN,
+             launch_attn_bf16(s, q, layer_kv(ctx, kv, l), attn, M, pos0, d.n_q_heads, d.n_kv_heads, hd,
+                              ctx->attn_part, ctx->attn_part_floats, lo ? &al : nullptr));
+      if (lo && al.n_parts > 0) {
+        p.lb[0] = (const bf16 *)lora[l].B[CRF_O];
+        p.upart_cols = rp;
+        p.upart_n = al.n_parts;
+      } else if (lo) {  // a short prefix: attention in one launch, without a merge
+        LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(attn, dq, CRF_O, p));
+      }
+      p.w[0] = (const bf16 *)w.w[CRF_O];
+      LAUNCH(ctx, s, CRF_KK_GEMM_O, launch_gemm_skinny_bf16(s, EPI_RESID, p));
+    }
+    {
+      GemmParams p = params(xn, D, 2 * f);
+      p.w[0] = (const bf16 *)w.w[CRF_GATE];
+      p.w[1] = (const bf16 *)w.w[CRF_UP];
+      p.act = act;
+      p.d_ffn = f;
+      LAUNCH(ctx, s, CRF_KK_NORM, norm(w.mlp_norm, false, CRF_GATE, 2, 0, p));
+      LAUNCH(ctx, s, CRF_KK_GEMM_GATEUP, launch_gemm_skinny_bf16(s, EPI_SWIGLU, p));
+    }
+    {
+      GemmParams p = params(act, f, D);
+      p.w[0] = (const bf16 *)w.w[CRF_DOWN];
+      p.resid_out = last ? (bf16 *)hout : nullptr;
+      if (has_lora(lora, l, CRF_DOWN)) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(act, f, CRF_DOWN, p));
+      LAUNCH(ctx, s, CRF_KK_GEMM_DOWN, launch_gemm_skinny_bf16(s, EPI_RESID, p));
+    }
+  }
+  return CRF_OK;
+}
+
 // Layers [l0, l0+h) over `rows` token rows at positions pos0..pos0+rows-1: a
 // window (pos0 = 0, rows = the prefix) or new tokens over a cached prefix
 // (pos0 = the prefix length).  kv_tail: without hidden_out the last layer runs
@@ -450,6 +572,7 @@ bool mid_rows(const crf_context *ctx, int rows) {
 crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_weights *W,
                            const crf_lora_layer *lora, int l0, int h, const crf_kv_cache *kv, void *hout,
                            hipStream_t s, int rows, int pos0, bool kv_tail) {
+  if (rows <= 16) return run_layers_few(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
   if (mid_rows(ctx, rows)) return run_layers_mid(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
   const crf_model_dims &d = ctx->dims;
   const int M = rows, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
@@ -492,33 +615,21 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       return p;
     };
     LoraDownTarget tg[3];
-    // a few token rows (a decoding step, a very short window): weight-streaming kernels
-    const bool skinny = M <= 16;
-    LoraSplit lsplit;  // set by the last LoRA down-projection
-    auto gemm = [&](GemmEpi epi, GemmParams &p) {
-      if (!skinny) return launch_gemm_bf16(s, epi, hd, p);
-      p.proj = ctx->proj16;
-      if (p.U && lsplit.n_parts > 0) {  // U still as K-split partials: the projection sums them
-        p.upart = ctx->lora_part;
-        p.upart_n = lsplit.n_parts;
-        p.upart_cols = lsplit.cols;
-        p.uscale = scale;
-      }
-      return launch_gemm_skinny_bf16(s, epi, hd, p);
+    auto lora_down = [&](const bf16 *x, int K, int n) {
+      return launch_lora_down_bf16(s, x, K, M, K, tg, n, rp, u, ldu, nullptr, 0, nullptr, lora_ws(ctx));
     };
+    auto gemm = [&](GemmEpi epi, const GemmParams &p) { return launch_gemm_bf16(s, epi, hd, p); };
 
     // attention block
-    // the window's first O projection reads the bf16 boundary state as its old
-    // residual (the weight-streaming kernels of a few rows read the fp32 copy)
-    const bool resid_from_boundary = first && !skinny;
+    // the window's first O projection reads the bf16 boundary state as its old residual
     LAUNCH(ctx, s, CRF_KK_NORM,
            launch_rmsnorm(s, first ? hb : (const void *)ctx->hres, !first, w.attn_norm, xn,
-                          first && !resid_from_boundary ? ctx->hres : nullptr, M, D, d.rms_eps));
+                          nullptr, M, D, d.rms_eps));
     if (last && !hout && kv_tail) {
       // Nothing reads this layer's output: its cache entry depends only on its
       // input through the K and V projections, so only those run.
       const bool kv_any = lora_targets({CRF_K, CRF_V}, tg);
-      if (kv_any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
+      if (kv_any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(xn, D, 2));
       GemmParams p = base_params(xn, D, 2 * dkv);
       p.w[1] = (const bf16 *)w.w[CRF_K];
       p.w[2] = (const bf16 *)w.w[CRF_V];
@@ -540,7 +651,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       break;
     }
     bool any = lora_targets({CRF_Q, CRF_K, CRF_V}, tg);
-    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 3, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
+    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(xn, D, 3));
     {
       GemmParams p = base_params(xn, D, dq + 2 * dkv);
       p.w[0] = (const bf16 *)w.w[CRF_Q];
@@ -568,7 +679,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
            launch_attn_bf16(s, q, layer_kv(ctx, kv, l), attn, M, pos0, d.n_q_heads, d.n_kv_heads, hd,
                             ctx->attn_part, ctx->attn_part_floats));
     any = lora_targets({CRF_O}, tg);
-    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, attn, dq, M, dq, tg, 1, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
+    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(attn, dq, 1));
     {
       GemmParams p = base_params(attn, dq, D);
       p.w[0] = (const bf16 *)w.w[CRF_O];
@@ -578,7 +689,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
         p.ucol[0] = 0;
       }
       p.resid = ctx->hres;
-      p.resid_in = resid_from_boundary ? (const bf16 *)hb : nullptr;
+      p.resid_in = first ? (const bf16 *)hb : nullptr;
       p.ldr = D;
       LAUNCH(ctx, s, CRF_KK_GEMM_O, gemm(EPI_RESID, p));
     }
@@ -586,7 +697,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
     LAUNCH(ctx, s, CRF_KK_NORM,
            launch_rmsnorm(s, ctx->hres, true, w.mlp_norm, xn, nullptr, M, D, d.rms_eps));
     any = lora_targets({CRF_GATE, CRF_UP}, tg);
-    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, xn, D, M, D, tg, 2, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
+    if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(xn, D, 2));
     // the down projection's adapter down-projection rides on the gate/up
     // epilogue when its rank fits (dn_done), else it is a pass of its own
     bool dn_done = false;
@@ -604,20 +715,20 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       }
       p.act = act;
       p.d_ffn = f;
-      if (!skinny && has_lora(lora, l, CRF_DOWN) && rank <= 16 && ctx->dn_part) {
+      if (has_lora(lora, l, CRF_DOWN) && rank <= 16 && ctx->dn_part) {
         p.dn_a = (const bf16 *)lora[l].A[CRF_DOWN];
         p.dn_rank = rank;
         p.dn_part = ctx->dn_part;
         p.dn_head = ctx->dn_head;
         p.dn_runs = DN_RUNS;
       }
-      LAUNCH(ctx, s, CRF_KK_GEMM_GATEUP, skinny ? gemm(EPI_SWIGLU, p) : launch_gemm_bf16(s, EPI_SWIGLU, hd, p, &dn_done));
+      LAUNCH(ctx, s, CRF_KK_GEMM_GATEUP, launch_gemm_bf16(s, EPI_SWIGLU, hd, p, &dn_done));
     }
     any = lora_targets({CRF_DOWN}, tg);
     if (any && dn_done)
       LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_gemm_dn_sum(s, pgu, u, ldu, 0, scale));
     else if (any)
-      LAUNCH(ctx, s, CRF_KK_LORA_DOWN, launch_lora_down_bf16(s, act, f, M, f, tg, 1, rp, u, ldu, ctx->lora_part, ctx->lora_part_floats, &lsplit, lora_ws(ctx)));
+      LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(act, f, 1));
     {
       GemmParams p = base_params(act, f, D);
       p.w[0] = (const bf16 *)w.w[CRF_DOWN];
@@ -628,7 +739,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       }
       p.resid = ctx->hres;
       p.resid_out = (last && hout) ? (bf16 *)hout : nullptr;
-      p.resid_final = p.resid_out && !skinny;  // nothing reads the fp32 residual after the window
+      p.resid_final = p.resid_out != nullptr;  // nothing reads the fp32 residual after the window
       p.ldr = D;
       LAUNCH(ctx, s, CRF_KK_GEMM_DOWN, gemm(EPI_RESID, p));
     }
@@ -914,7 +1025,7 @@ crf_status crf_validate_window(const crf_model_dims *dims, int32_t l0, int32_t h
 void crf_context_destroy(crf_context *ctx) {
   if (!ctx) return;
   void *bufs[] = {ctx->hres, ctx->xn, ctx->q, ctx->attn, ctx->act, ctx->u, ctx->rope_cs,
-                  ctx->d_err, ctx->drift_dev, ctx->proj16, ctx->attn_part, ctx->lora_part, ctx->gemm_part,
+                  ctx->d_err, ctx->drift_dev, ctx->attn_part, ctx->lora_part, ctx->gemm_part,
                   ctx->dn_part, ctx->dn_head, ctx->tickets};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
@@ -963,7 +1074,6 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
   if ((st = dmalloc(ctx, &ctx->act, T * f * e)) != CRF_OK) return cleanup(st);
   if (dims->dtype == CRF_BF16) {
     if ((st = dmalloc(ctx, &ctx->u, T * 3 * ctx->rank_pad * 2)) != CRF_OK) return cleanup(st);
-    if ((st = dmalloc(ctx, &ctx->proj16, 16 * (dq + 2 * dkv) * 4)) != CRF_OK) return cleanup(st);
     // key splits of >= 64 keys, up to 16 query rows per head, rows of hd + 4 floats
     ctx->attn_part_floats = (int64_t)((T + 63) / 64) * dims->n_q_heads * 16 * (dims->head_dim + 4);
     // ... and for a prefix long enough to be split under whole query blocks, a
@@ -971,8 +1081,9 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
     if (T >= 2048)
       ctx->attn_part_floats = std::max<int64_t>(ctx->attn_part_floats, (int64_t)512 * 128 * (dims->head_dim + 4));
     if ((st = dmalloc(ctx, &ctx->attn_part, (size_t)ctx->attn_part_floats * 4)) != CRF_OK) return cleanup(st);
-    // K splits of >= 256 for up to 16 rows and three targets
-    ctx->lora_part_floats = (int64_t)((std::max({D, f, dq}) + 255) / 256) * 16 * 3 * ctx->rank_pad;
+    // K parts of >= 256, or one per query head, for up to 16 rows and three targets
+    ctx->lora_part_floats =
+        (int64_t)std::max<size_t>((std::max({D, f, dq}) + 255) / 256, dims->n_q_heads) * 16 * 3 * ctx->rank_pad;
     if ((st = dmalloc(ctx, &ctx->lora_part, (size_t)ctx->lora_part_floats * 4)) != CRF_OK) return cleanup(st);
     // at most one 256x256 fp32 partial per compute unit
     if (hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
@@ -1163,7 +1274,7 @@ crf_status crf_decode_logits(crf_context *ctx, const crf_model_dims *dims, const
   p.resid = logits_out;
   p.ldr = vocab;
   p.resid_overwrite = 1;
-  LAUNCH(ctx, s, CRF_KK_OTHER, launch_gemm_skinny_bf16(s, EPI_RESID, d.head_dim, p));
+  LAUNCH(ctx, s, CRF_KK_OTHER, launch_gemm_skinny_bf16(s, EPI_RESID, p));
   return CRF_OK;
 }
 

@@ -57,7 +57,10 @@ constexpr int NT = 64 * NW;         // threads per workgroup
 constexpr int BKV = 64;   // keys per tile
 constexpr float PSUM_MAX = 256.0f;  // bound on a half-block's probability sum (and each probability)
 constexpr int PGCAP = 2048;  // page bases staged in LDS at a time
-constexpr int SPLIT_WG = 1024;  // workgroups aimed at when a few query rows are split over the keys
+// Workgroups aimed at when a few query rows are split over the keys: the
+// resident ones (16385 keys, 4 KV heads of 128: 1024 -> 12.3 + 6.0 us with the
+// merge, 512 -> 11.0 + 4.8, 384 the same).
+constexpr int SPLIT_WG = 512;
 constexpr int ATTN_SLOTS = 512;  // resident workgroups of the GPU (two per CU)
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -470,53 +473,95 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
 
 // Merge of the key splits of one (query row, head): O = sum_s 2^(m_s - m) O_s /
 // sum_s 2^(m_s - m) l_s with m = max_s m_s (scores in log2 units).  Groups of
-// HD / 4 threads take every NG-th split, 4 output elements per thread.
+// HD / 4 threads take every NG-th split, 4 output elements per thread, with the
+// group's own running maximum (no pass over the maxima first), four splits'
+// loads in flight.
 template <int HD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ part, bf16 *__restrict__ O,
-                                                         int Mq, int nq, int n_splits) {
-  constexpr int TPG = HD / 4, NG = 256 / TPG;
-  __shared__ float wmax[4];
+                                                         int Mq, int nq, int n_splits, const AttnLora lora) {
+  constexpr int TPG = HD / 4, NG = 256 / TPG, UN = 4;
   __shared__ f32x4 osum[NG][TPG];
-  __shared__ float lsum[NG];
+  __shared__ float lsum[NG], gmax[NG];
   const int qi = blockIdx.x / nq, head = blockIdx.x % nq;
   const int tid = threadIdx.x;
   const int64_t stride = (int64_t)nq * Mq * (HD + 4);
   const float *p0 = part + ((int64_t)head * Mq + qi) * (HD + 4);
-  float m = -INFINITY;
-  for (int sp = tid; sp < n_splits; sp += 256) m = fmaxf(m, p0[sp * stride + HD]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-  if (tid % 64 == 0) wmax[tid / 64] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
   const int gi = tid / TPG, e = 4 * (tid % TPG);
   f32x4 o = {0.f, 0.f, 0.f, 0.f};
-  float l = 0.f;
-#pragma unroll 4
-  for (int sp = gi; sp < n_splits; sp += NG) {
-    const float *ps = p0 + sp * stride;
-    const float w = exp2f(ps[HD] - m);
-    l += w * ps[HD + 1];
-    o += w * *reinterpret_cast<const f32x4 *>(ps + e);
+  float l = 0.f, m = -INFINITY;
+  for (int sp0 = gi; sp0 < n_splits; sp0 += UN * NG) {
+    f32x4 t[UN];
+    float ms[UN], ls[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {  // past the end: the last split again, of weight 0
+      const int sp = sp0 + u * NG;
+      const float *ps = p0 + min(sp, n_splits - 1) * stride;
+      t[u] = *reinterpret_cast<const f32x4 *>(ps + e);
+      ms[u] = sp < n_splits ? ps[HD] : -INFINITY;
+      ls[u] = ps[HD + 1];
+    }
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) mn = fmaxf(mn, ms[u]);  // finite: the first split of a batch is a real one
+    const float a = exp2f(m - mn);
+    o *= a;
+    l *= a;
+    m = mn;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const float w = exp2f(ms[u] - mn);
+      l += w * ls[u];
+      o += w * t[u];
+    }
   }
   osum[gi][tid % TPG] = o;
-  if (tid % TPG == 0) lsum[gi] = l;
-  __syncthreads();
-  if (tid >= TPG) return;
-  f32x4 ot = osum[0][tid];
-  float lt = lsum[0];
-#pragma unroll
-  for (int g2 = 1; g2 < NG; ++g2) {
-    ot += osum[g2][tid];
-    lt += lsum[g2];
+  if (tid % TPG == 0) {
+    lsum[gi] = l;
+    gmax[gi] = m;
   }
-  const float inv = 1.0f / lt;
-  st8(O + (int64_t)qi * nq * HD + head * HD + e, pack_bf16x4(ot[0] * inv, ot[1] * inv, ot[2] * inv, ot[3] * inv));
+  __syncthreads();
+  __shared__ __align__(16) bf16 osh[HD];
+  if (tid < TPG) {
+    float mt = gmax[0];
+#pragma unroll
+    for (int g2 = 1; g2 < NG; ++g2) mt = fmaxf(mt, gmax[g2]);
+    f32x4 ot = {0.f, 0.f, 0.f, 0.f};
+    float lt = 0.f;
+#pragma unroll
+    for (int g2 = 0; g2 < NG; ++g2) {
+      const float w = exp2f(gmax[g2] - mt);  // (a group without a split weighs 0)
+      ot += w * osum[g2][tid];
+      lt += w * lsum[g2];
+    }
+    const float inv = 1.0f / lt;
+    const u32x2 o4 = pack_bf16x4(ot[0] * inv, ot[1] * inv, ot[2] * inv, ot[3] * inv);
+    st8(O + (int64_t)qi * nq * HD + head * HD + e, o4);
+    st8(&osh[e], o4);
+  }
+  if (!lora.A) return;
+  // this head's part of the output adapter's U: HD / 8 lanes per rank
+  constexpr int LPK = HD / 8;
+  const int l8 = tid % LPK;
+  u32x4 a0 = {0u, 0u, 0u, 0u};
+  const bf16 *ap = lora.A + (int64_t)(tid / LPK) * nq * HD + head * HD + 8 * l8;
+  if (tid / LPK < lora.rank) a0 = ld16(ap);
+  __syncthreads();
+  const bf16x8 x = as_bf16x8(ld16(&osh[8 * l8]));
+  for (int r = tid / LPK; r < lora.rank; r += 256 / LPK) {
+    const bf16x8 a = as_bf16x8(a0);
+    if (r + 256 / LPK < lora.rank) a0 = ld16(ap += (int64_t)(256 / LPK) * nq * HD);
+    float v = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v = fmaf(bf2f(a[i]), bf2f(x[i]), v);
+#pragma unroll
+    for (int o = LPK / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, LPK);
+    if (l8 == 0) lora.part[((int64_t)head * 16 + qi) * lora.cols + r] = v;
+  }
 }
 
 template <int HD>
 void launch(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, int q_off, int nq, int nkv,
-            uint32_t pool_bytes, float *part, int64_t part_floats) {
+            uint32_t pool_bytes, float *part, int64_t part_floats, AttnLora *lora) {
   const int nqb = (Mq + BQ - 1) / BQ;
   int xcd_r = 0, grid = nqb * nq, n_splits = 1, split_tiles = 0, packed = 0;
   const int64_t keys = (int64_t)q_off + Mq;
@@ -549,22 +594,26 @@ void launch(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, in
   else
     hipLaunchKernelGGL((attn_bf16_kernel<HD, 0>), g3, dim3(NT), 0, s, Q, kv, O, Mq, q_off, nq, nkv, pool_bytes,
                        xcd_r, split_tiles, n_splits, packed, part);
-  if (split_tiles > 0)
-    hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(Mq * nq), dim3(256), 0, s, part, O, Mq, nq, n_splits);
+  if (split_tiles > 0) {
+    if (lora && Mq <= 16) lora->n_parts = nq;
+    const AttnLora al = lora && Mq <= 16 ? *lora : AttnLora{};
+    hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(Mq * nq), dim3(256), 0, s, part, O, Mq, nq, n_splits, al);
+  }
 }
 
 }  // namespace
 
 hipError_t launch_attn_bf16(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, int q_off, int nq,
-                            int nkv, int hd, float *part, int64_t part_floats) {
+                            int nkv, int hd, float *part, int64_t part_floats, AttnLora *lora) {
+  if (lora) lora->n_parts = 0;
   if (Mq <= 0) return hipSuccess;
   if (q_off < 0) return hipErrorInvalidValue;
   const int64_t bytes = (int64_t)kv.n_pages * kv.page_stride * 2;
   if (bytes >= (int64_t)CRF_OOB) return hipErrorInvalidValue;
   if (hd == 128)
-    launch<128>(s, Q, kv, O, Mq, q_off, nq, nkv, (uint32_t)bytes, part, part_floats);
+    launch<128>(s, Q, kv, O, Mq, q_off, nq, nkv, (uint32_t)bytes, part, part_floats, lora);
   else if (hd == 64)
-    launch<64>(s, Q, kv, O, Mq, q_off, nq, nkv, (uint32_t)bytes, part, part_floats);
+    launch<64>(s, Q, kv, O, Mq, q_off, nq, nkv, (uint32_t)bytes, part, part_floats, lora);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

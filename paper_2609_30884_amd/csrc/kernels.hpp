@@ -62,17 +62,11 @@ struct LoraDownTarget {
 };
 // U[m, ucol_t + j] = bf16(scale_t * sum_k X[m,k] A_t[j,k]) for j < rank_pad(t)
 // (zero for rank <= j < rank_pad).
-// ws (nullable, ws_floats floats): workspace for splitting K over workgroups
-// when M <= 16.  With `split` non-null, a split into at most four parts is
-// left as unscaled fp32 partials in ws ([part][16][n_targets * rank_pad]) for
-// the consuming projection to sum (split->n_parts > 0; U is not written);
-// otherwise split->n_parts = 0 and U holds the result.
-struct LoraSplit {
-  int n_parts = 0;
-  int cols = 0;
-};
-// For M > 16, workspace to split K over workgroups: `floats` floats, and
-// n_tickets counters that are zero between launches.
+// M <= 16: U is not formed; unscaled fp32 parts of it are left in ws
+// ([part][16][n_targets * rank_pad], ws_floats floats), *n_parts of them, for
+// the projection to sum.  M > 16: `lw` (nullable blocks) lets K be split over
+// workgroups, in `floats` floats and n_tickets counters that are zero between
+// launches.
 struct LoraWs {
   float *blocks = nullptr;
   int64_t floats = 0;
@@ -81,7 +75,7 @@ struct LoraWs {
 };
 hipError_t launch_lora_down_bf16(hipStream_t s, const bf16 *X, int64_t ldx, int M, int K, const LoraDownTarget *t,
                                  int n_targets, int rank_pad, bf16 *U, int ldu, float *ws, int64_t ws_floats,
-                                 LoraSplit *split, const LoraWs &lw);
+                                 int *n_parts, const LoraWs &lw);
 
 enum GemmEpi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
 
@@ -100,7 +94,7 @@ struct GemmParams {
   // EPI_QKV
   const bf16 *bias[3];
   bf16 *q_out;
-  int dq;
+  int dq, hd;
   float q_scale;               // factor applied to Q (after bias and rotary) before it is stored
   PagedKV kv;
   const float2 *rope_cs;
@@ -119,10 +113,8 @@ struct GemmParams {
   // EPI_SWIGLU: act[m, f] = silu(gate) * up
   bf16 *act;
   int d_ffn;
-  // EPI_QKV with few token rows: fp32 projections [M, N] before the rotary/paged stores
-  float *proj;
-  // few token rows: U given as unscaled K-split partials ([part][16][upart_cols]
-  // fp32, upart_n parts) to be summed, scaled by uscale and rounded to bf16
+  // few token rows: U given as unscaled K-split parts ([part][16][upart_cols]
+  // fp32, upart_n > 0 parts) to be summed, scaled by uscale and rounded to bf16
   const float *upart;
   int upart_n, upart_cols;
   float uscale;
@@ -133,6 +125,10 @@ struct GemmParams {
   // set by the launcher.
   float *split_part;
   int64_t split_cap;
+  // few token rows: arrival counters of K-split workgroups, zero between launches
+  unsigned *tickets;
+  int n_tickets;
+  int kpairs;  // pairs of k-steps per part, set by the launcher
   int n_cu;
   int split_first, split_s;
   // EPI_SWIGLU: the down projection's adapter down-projection fused into the
@@ -155,7 +151,23 @@ hipError_t launch_gemm_bf16(hipStream_t s, GemmEpi epi, int hd, const GemmParams
 // launch_gemm_bf16(EPI_SWIGLU) reported *dn_done with the same parameters.
 hipError_t launch_gemm_dn_sum(hipStream_t s, const GemmParams &p, bf16 *U, int ldu, int ucol, float scale);
 // The same projections for M <= 16 token rows (weight-streaming bound).
-hipError_t launch_gemm_skinny_bf16(hipStream_t s, GemmEpi epi, int hd, const GemmParams &p);
+hipError_t launch_gemm_skinny_bf16(hipStream_t s, GemmEpi epi, const GemmParams &p);
+// y = RMSNorm(x) g of up to 16 rows (copy_out, nullable, receives x in fp32)
+// with the adapters' down-projection of y: part[s][16][n_blocks * 16] unscaled,
+// s < norm_lora_parts(d); n_blocks = targets * rank_pad / 16 (0: no adapter).
+struct NormLora {
+  const void *x;
+  const bf16 *g;
+  bf16 *y;
+  float *copy_out;
+  int M, d;
+  float eps;
+  const bf16 *A[3];  // [rank, d] or null
+  int rank, rank_pad;
+  float *part;
+};
+int norm_lora_parts(int d);
+hipError_t launch_norm_lora(hipStream_t s, bool x_f32, const NormLora &p, int n_blocks);
 
 // ---- 17 to MID_MAX_ROWS token rows (gemm_mid.hip)
 constexpr int MID_SEGS = 6;       // row sources of a launch: up to three weights, then their A factors
@@ -215,9 +227,17 @@ inline float attn_query_scale(int hd) { return 1.4426950408889634f / __builtin_s
 // Query rows 0..Mq-1 at positions q_off..q_off+Mq-1 over keys 0..q_off+Mq-1,
 // Q pre-multiplied by attn_query_scale(hd).
 // part (nullable, part_floats floats): workspace for splitting a few query
-// rows (<= 16) over the keys of a long prefix.
+// rows (<= 16) over the keys of a long prefix.  With `lora` (Mq <= 16) and a
+// split launch the merge also forms the parts of O A^T, one per query head
+// (lora->n_parts set; else it stays 0).
+struct AttnLora {
+  const bf16 *A;   // [rank, nq * hd]
+  int rank, cols;  // part[head][16][cols]
+  float *part;
+  int n_parts;
+};
 hipError_t launch_attn_bf16(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, int q_off, int nq,
-                            int nkv, int hd, float *part, int64_t part_floats);
+                            int nkv, int hd, float *part, int64_t part_floats, AttnLora *lora = nullptr);
 
 // ---------------------------------------------------------------- drift
 // One factor tensor of the current adapter; the same tensor of the stored

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * NW) void lora_down_kernel(LdArgs a) {
       continue;
     }
     if (m >= a.M) continue;
-    if (a.part) {  // K split over workgroups: unscaled partial, summed by lora_down_sum_kernel
+    if (a.part) {  // K split over workgroups: unscaled part, summed by the projection
       const int ncols = a.n_targets * a.rank_pad;
       *reinterpret_cast<f32x4 *>(a.part + ((int64_t)blockIdx.y * 16 + m) * ncols + b * 16 + (lane / 16) * 4) = v;
       continue;
@@ -149,44 +149,20 @@ __global__ __launch_bounds__(64 * NW) void lora_down_kernel(LdArgs a) {
   }
 }
 
-// U[m, ucol_t + j] = scale_t * sum over the K split of the partials (M <= 16).
-// 16 lanes per output, lane l adding the parts l, l + 16, ...; the 16 sums are
-// then combined in a fixed order.
-__global__ __launch_bounds__(256) void lora_down_sum_kernel(LdArgs a, int n_split) {
-  const int ncols = a.n_targets * a.rank_pad;
-  const int o = blockIdx.x * 16 + threadIdx.x / 16, l = threadIdx.x % 16;
-  float v = 0.f;
-  if (o < a.M * ncols) {
-    const int m = o / ncols, c = o % ncols;
-    for (int y = l; y < n_split; y += 16) v += a.part[((int64_t)y * 16 + m) * ncols + c];
-  }
-#pragma unroll
-  for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 16);
-  if (l != 0 || o >= a.M * ncols) return;
-  const int m = o / ncols, c = o % ncols;
-  const int t = c / a.rank_pad, j = c % a.rank_pad;
-  a.U[(int64_t)m * a.ldu + a.ucol[t] + j] = f2bf(v * a.scale[t]);
-}
-
 template <int NB>
-void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *few, const LoraWs &lw) {
+hipError_t go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, int *n_parts, const LoraWs &lw) {
   constexpr int UNROLL = NB <= 4 ? 8 : 2;
   const int nsteps = a.K / 32;
-  // a few token rows: split K over workgroups (one batch of loads per wave)
-  // and sum the partials in a second, tiny kernel
-  const int spw = 4 * UNROLL, n_split = (nsteps + spw - 1) / spw;
-  if (a.M <= 16 && n_split > 1 && ws && (int64_t)n_split * 16 * a.n_targets * a.rank_pad <= ws_floats) {
-    a.spw = spw;
+  if (a.M <= 16) {
+    // a few token rows: K split over workgroups (one batch of loads per wave),
+    // the parts summed by the projection that uses U
+    a.spw = 4 * UNROLL;
+    const int n = (nsteps + a.spw - 1) / a.spw;
+    if (!n_parts || !ws || (int64_t)n * 16 * a.n_targets * a.rank_pad > ws_floats) return hipErrorInvalidValue;
     a.part = ws;
-    hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(1, n_split), dim3(256), 0, s, a);
-    if (few && n_split <= 4) {  // the consumer sums the partials
-      few->n_parts = n_split;
-      few->cols = a.n_targets * a.rank_pad;
-      return;
-    }
-    hipLaunchKernelGGL(lora_down_sum_kernel, dim3((a.M * a.n_targets * a.rank_pad + 15) / 16), dim3(256), 0, s, a,
-                       n_split);
-    return;
+    *n_parts = n;
+    hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(1, n), dim3(256), 0, s, a);
+    return hipSuccess;
   }
   a.spw = nsteps;
   a.part = nullptr;
@@ -195,7 +171,7 @@ void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *few, c
       // 64 tokens per workgroup (the factors are read once per 64 tokens) and
       // 8 waves splitting K, so that enough loads are in flight per CU
       hipLaunchKernelGGL((lora_down_kernel<NB, 4, 4, 8>), dim3((a.M + 63) / 64), dim3(512), 0, s, a);
-      return;
+      return hipSuccess;
     }
   }
   // Fewer tokens: 16 per workgroup.  A workgroup is bound by what one CU can
@@ -212,17 +188,18 @@ void go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, LoraSplit *few, c
     a.tickets = lw.tickets;
     a.blocks = lw.blocks;
     hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(mb, (nsteps + a.spw - 1) / a.spw), dim3(256), 0, s, a);
-    return;
+    return hipSuccess;
   }
   hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(mb), dim3(256), 0, s, a);
+  return hipSuccess;
 }
 
 }  // namespace
 
 hipError_t launch_lora_down_bf16(hipStream_t s, const bf16 *X, int64_t ldx, int M, int K, const LoraDownTarget *t,
                                  int n_targets, int rank_pad, bf16 *U, int ldu, float *ws, int64_t ws_floats,
-                                 LoraSplit *split, const LoraWs &lw) {
-  if (split) *split = LoraSplit{};
+                                 int *n_parts, const LoraWs &lw) {
+  if (n_parts) *n_parts = 0;
   if (M <= 0 || n_targets <= 0) return hipSuccess;
   if (n_targets > MAXT || n_targets * rank_pad > MAXB * 16 || rank_pad % 16 || K % 32) return hipErrorInvalidValue;
   LdArgs a{};
@@ -240,18 +217,19 @@ hipError_t launch_lora_down_bf16(hipStream_t s, const bf16 *X, int64_t ldx, int 
   a.rank_pad = rank_pad;
   a.U = U;
   a.ldu = ldu;
+  hipError_t e;
   switch (n_targets * rank_pad / 16) {
-    case 1: go<1>(s, a, ws, ws_floats, split, lw); break;
-    case 2: go<2>(s, a, ws, ws_floats, split, lw); break;
-    case 3: go<3>(s, a, ws, ws_floats, split, lw); break;
-    case 4: go<4>(s, a, ws, ws_floats, split, lw); break;
-    case 6: go<6>(s, a, ws, ws_floats, split, lw); break;
-    case 8: go<8>(s, a, ws, ws_floats, split, lw); break;
-    case 9: go<9>(s, a, ws, ws_floats, split, lw); break;
-    case 12: go<12>(s, a, ws, ws_floats, split, lw); break;
+    case 1: e = go<1>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 2: e = go<2>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 3: e = go<3>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 4: e = go<4>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 6: e = go<6>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 8: e = go<8>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 9: e = go<9>(s, a, ws, ws_floats, n_parts, lw); break;
+    case 12: e = go<12>(s, a, ws, ws_floats, n_parts, lw); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace crf
