@@ -728,6 +728,13 @@ __global__ __launch_bounds__(256) void dn_sum_kernel(const GemmParams p, const S
     if (r + q < p.dn_rank) u[q] = f2bf(v[q] * scale);
 }
 
+// K slices from which three K-parts in two rounds beat one round more than half
+// full (the third of a round saved, 0.5 us a slice, against about 50 us for the
+// partials): down projections, two layers of 1.5B shapes (140 slices) over 5600
+// tokens 1620 -> 1578 us, 7168: 1827 -> 1800; one of 7B shapes (296) over 2600
+// tokens 1478 -> 1412, 12000: 6310 -> 6250.
+constexpr int SPLIT3_SLICES = 96;
+
 Sched schedule(GemmEpi epi, const GemmParams &p) {
   Sched sc{};
   sc.tiles_m = (p.M + BM - 1) / BM;
@@ -737,16 +744,21 @@ Sched schedule(GemmEpi epi, const GemmParams &p) {
   sc.split_first = tiles;
   sc.split_s = 1;
   if ((epi == EPI_RESID || epi == EPI_QKV) && p.split_part && p.n_cu > 0) {
-    // a last wave at most half full: split its tiles (or all tiles, when there
-    // are fewer than compute units) into K-parts of at least 8 slices
+    // a last wave at most half full: split its tiles (all tiles, when there are
+    // fewer than compute units) into K-parts of at least 8 slices, as many as
+    // there are compute units for: a slice of a tile costs 1.6 us and a part's
+    // write and read about 0.1 us (against two parts, 1.5B shapes over 12288
+    // tokens 3345 -> 3234 us for two layers, 7B shapes over 5200 tokens 2740 ->
+    // 2610 for one).  Up to two thirds full, three parts run in two rounds, which
+    // pays with a long K.
     const int r = tiles % p.n_cu;
     int first = tiles, sp = 1;
-    if (tiles < p.n_cu) {
-      first = 0;
-      sp = p.n_cu / tiles;
-    } else if (r > 0 && 2 * r <= p.n_cu) {
+    if (r > 0 && 2 * r <= p.n_cu) {
       first = tiles - r;
-      sp = 2;
+      sp = p.n_cu / r;
+    } else if (r > 0 && 3 * r <= 2 * p.n_cu && sc.nk >= SPLIT3_SLICES) {
+      first = tiles - r;
+      sp = 3;
     }
     sp = std::min(sp, std::min(8, sc.nk / 8));
     if (sp >= 2 && (int64_t)(tiles - first) * sp * BM * BN <= p.split_cap) {
