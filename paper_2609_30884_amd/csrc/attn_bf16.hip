@@ -161,12 +161,44 @@ inline int attn_split_grid(int nq, int nkv, int nqb, int n_splits, int packed) {
   return 8 * ((nkv * n_splits + 7) / 8) * (packed ? 1 : nq / nkv * nqb);
 }
 
+// Window launch whose query blocks from `long0` on have their keys in two parts
+// (per-XCD order, xcd_r > 0): query head, query block and part of workgroup
+// `bid`; false for padding.  Longest first along an XCD's list: the first parts
+// of its long blocks, then their second parts and the short blocks in turn.
+__host__ __device__ inline bool attn_halves_block(int bid, int nq, int nkv, int nqb, int xcd_r, int long0, int &head,
+                                                  int &qblk, int &split) {
+  const int group = nq / nkv, x = bid % 8, r = x % xcd_r, j = bid / 8;
+  head = (x / xcd_r) * group + j % group;
+  const int last = nqb - 1 - r;  // the XCD's longest block; its others are xcd_r apart
+  const int blocks = last < 0 ? 0 : last / xcd_r + 1, n_long = last < long0 ? 0 : (last - long0) / xcd_r + 1;
+  int q = j / group;
+  if (q >= blocks + n_long) return false;
+  split = 0;
+  if (q >= n_long) {
+    q -= n_long;
+    const int n_short = blocks - n_long, both = 2 * (n_long < n_short ? n_long : n_short);
+    if (q < both) {
+      split = (q & 1) == 0;
+      q = split ? q / 2 : n_long + q / 2;
+    } else if (n_long > n_short) {
+      split = 1;
+      q -= n_short;
+    }  // else short block q - n_long of the list, whose index is q
+  }
+  qblk = last - q * xcd_r;
+  return true;
+}
+
+inline int attn_halves_grid(int nq, int nkv, int nqb, int xcd_r, int long0) {
+  return 8 * (nq / nkv) * ((nqb + xcd_r - 1) / xcd_r + (nqb - long0 + xcd_r - 1) / xcd_r);
+}
+
 // PS: page size when fixed at compile time (16), 0 = runtime kv.page_size.
 template <int HD, int PS>
 __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__restrict__ Q, PagedKV kv,
                                                            bf16 *__restrict__ O, int Mq, int q_off, int nq,
                                                            int nkv, uint32_t pool_bytes, int xcd_r,
-                                                           int split_tiles, int n_splits, int packed,
+                                                           int split_tiles, int n_splits, int packed, int long0,
                                                            float *__restrict__ part) {
   constexpr int CH = HD / 8;             // 16-byte chunks per row
   constexpr int KS = HD / 16;            // MFMA k-steps for S
@@ -187,7 +219,9 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
   const int nqb = (Mq + BQ - 1) / BQ;
   const int group = nq / nkv;
   int head, qblk, split = 0;
-  if (split_tiles > 0) {
+  if (long0 >= 0) {
+    if (!attn_halves_block(blockIdx.x, nq, nkv, nqb, xcd_r, long0, head, qblk, split)) return;
+  } else if (split_tiles > 0) {
     if (!attn_split_block(blockIdx.x, nq, nkv, nqb, n_splits, packed, head, qblk, split)) return;
   } else if (!attn_block(blockIdx.x, nq, nkv, nqb, xcd_r, packed, head, qblk)) {
     return;
@@ -226,9 +260,11 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
   const int ntiles = last_key / BKV + 1;
   // Split over keys (few query blocks over a long prefix): this workgroup takes
   // tiles [t_begin, t_end) and leaves an unnormalised partial for the merge (of
-  // weight 0 where the range lies past every key of its rows).
+  // weight 0 where the range lies past every key of its rows).  long0 >= 0: only
+  // the query blocks from long0 on are split.
+  const bool partial = split_tiles > 0 && qblk >= long0;
   int t_begin = 0, t_end = ntiles;
-  if (split_tiles > 0) {
+  if (partial) {
     t_begin = split * split_tiles;
     t_end = min(ntiles, t_begin + split_tiles);
   }
@@ -445,8 +481,9 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
 
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   if (qi >= n_rows) return;
-  if (split_tiles > 0) {  // partial: unnormalised O^T row, then the running max and sum
-    float *prow = part + (((int64_t)split * nq + qhead) * Mq + qrow) * (HD + 4);
+  if (partial) {  // unnormalised O^T row, then the running max and sum
+    const int row0 = max(long0, 0) * BQ;  // first row with partials
+    float *prow = part + (((int64_t)split * nq + qhead) * (Mq - row0) + qrow - row0) * (HD + 4);
 #pragma unroll
     for (int b = 0; b < HB; ++b)
 #pragma unroll
@@ -559,11 +596,55 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
   }
 }
 
+// The same for the two parts of every row from row0 on: HD / 4 lanes per (row,
+// head), 256 * 4 / HD of them to a workgroup.
+template <int HD>
+__global__ __launch_bounds__(256) void attn_halves_merge_kernel(const float *__restrict__ part, bf16 *__restrict__ O,
+                                                                int row0, int n_rows, int nq) {
+  constexpr int TPG = HD / 4;
+  const int64_t i = (int64_t)blockIdx.x * (256 / TPG) + threadIdx.x / TPG;  // row * nq + head
+  if (i >= (int64_t)n_rows * nq) return;
+  const int r = (int)(i / nq), head = (int)(i % nq), e = 4 * (threadIdx.x % TPG);
+  const float *p0 = part + ((int64_t)head * n_rows + r) * (HD + 4), *p1 = p0 + (int64_t)nq * n_rows * (HD + 4);
+  const f32x4 a = *reinterpret_cast<const f32x4 *>(p0 + e), b = *reinterpret_cast<const f32x4 *>(p1 + e);
+  const float ma = p0[HD], la = p0[HD + 1], mb = p1[HD], lb = p1[HD + 1];
+  const float m = fmaxf(ma, mb), wa = exp2f(ma - m), wb = exp2f(mb - m);
+  const float inv = 1.0f / (wa * la + wb * lb);
+  const f32x4 o = (wa * a + wb * b) * inv;
+  st8(O + (int64_t)(row0 + r) * nq * HD + head * HD + e, pack_bf16x4(o[0], o[1], o[2], o[3]));
+}
+
+// First query block whose keys a window launch takes in two parts of split_tiles
+// tiles (-1: none).  A workgroup alone on a CU computes a tile more slowly than a
+// CU with all its workgroups (two at head size 128, three at 64), so with few
+// blocks the longest chain of tiles outlasts the GPU's share of all tiles; the
+// parts cost 52 MB of partials at 4096 tokens of 12 heads (attention 94 -> 77 us
+// and a merge of 8).  The line, as the chain's tiles over a CU's share of all:
+// 12 heads of 128, 3000 tokens (1.7) 865 -> 843 us for two layers, 5000 (1.04)
+// 1285 -> 1276, 6100 (0.87) 1593 -> 1612; 28 heads, 2060 tokens (1.01) 1056 ->
+// 1070 for one; 12 heads of 64, 6100 tokens (0.87) 514 -> 501.
+inline int attn_halves(int Mq, int q_off, int nq, int nqb, int hd, int64_t part_floats, int &split_tiles) {
+  const int nt = (q_off + Mq + BKV - 1) / BKV, nt0 = (q_off + std::min(Mq, BQ) + BKV - 1) / BKV;
+  if (nt < 32) return -1;  // a part of at least 16 tiles
+  const double share = 0.5 * nq * nqb * (nt + nt0) / (ATTN_SLOTS / 2);
+  if (nt <= (hd == 128 ? 1.03 : 0.8) * share) return -1;
+  // the middle, or as far past it as the partials fit
+  for (int st = (nt + 1) / 2; st < nt; ++st) {
+    // blocks from here on end past tile st: q_off + (b + 1) * BQ > st * BKV
+    const int b = std::max(0, (int)(((int64_t)st * BKV - q_off) / BQ));
+    if (b >= nqb) break;
+    if (2 * (int64_t)nq * (Mq - b * BQ) * (hd + 4) > part_floats) continue;
+    split_tiles = st;
+    return b;
+  }
+  return -1;
+}
+
 template <int HD>
 void launch(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, int q_off, int nq, int nkv,
             uint32_t pool_bytes, float *part, int64_t part_floats, AttnLora *lora) {
   const int nqb = (Mq + BQ - 1) / BQ;
-  int xcd_r = 0, grid = nqb * nq, n_splits = 1, split_tiles = 0, packed = 0;
+  int xcd_r = 0, grid = nqb * nq, n_splits = 1, split_tiles = 0, packed = 0, long0 = -1;
   const int64_t keys = (int64_t)q_off + Mq;
   const int ntiles = (int)((keys + BKV - 1) / BKV);
   const int64_t max_splits = part ? part_floats / ((int64_t)nq * Mq * (HD + 4)) : 0;
@@ -586,15 +667,22 @@ void launch(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, in
     grid = attn_split_grid(nq, nkv, nqb, n_splits, packed);
   } else {
     grid = attn_window_grid(nq, nkv, nqb, xcd_r);
+    if (xcd_r > 0 && part) long0 = attn_halves(Mq, q_off, nq, nqb, HD, part_floats, split_tiles);
+    if (long0 >= 0) grid = attn_halves_grid(nq, nkv, nqb, xcd_r, long0);
   }
   const dim3 g3(grid);
   if (kv.page_size == 16)
     hipLaunchKernelGGL((attn_bf16_kernel<HD, 16>), g3, dim3(NT), 0, s, Q, kv, O, Mq, q_off, nq, nkv, pool_bytes,
-                       xcd_r, split_tiles, n_splits, packed, part);
+                       xcd_r, split_tiles, n_splits, packed, long0, part);
   else
     hipLaunchKernelGGL((attn_bf16_kernel<HD, 0>), g3, dim3(NT), 0, s, Q, kv, O, Mq, q_off, nq, nkv, pool_bytes,
-                       xcd_r, split_tiles, n_splits, packed, part);
-  if (split_tiles > 0) {
+                       xcd_r, split_tiles, n_splits, packed, long0, part);
+  if (long0 >= 0) {
+    const int rows = Mq - long0 * BQ;
+    const int64_t threads = (int64_t)rows * nq * (HD / 4);
+    hipLaunchKernelGGL((attn_halves_merge_kernel<HD>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, part, O,
+                       long0 * BQ, rows, nq);
+  } else if (split_tiles > 0) {
     if (lora && Mq <= 16) lora->n_parts = nq;
     const AttnLora al = lora && Mq <= 16 ? *lora : AttnLora{};
     hipLaunchKernelGGL((attn_merge_kernel<HD>), dim3(Mq * nq), dim3(256), 0, s, part, O, Mq, nq, n_splits, al);
