@@ -9,7 +9,7 @@
 // gate/up, down) where one kernel per operation took 20; every launch splits K
 // over the waves of a workgroup so that its chain of loads stays short.
 // Measured: 2 layers of d = 256 over 128 tokens (rank 8 on q, k, v, o) 966 ->
-// 66 us, 4 layers over 1511 tokens (rank 8 on all seven) 4399 -> 511 us (27
+// 66 us, 4 layers over 1511 tokens (rank 8 on all seven) 4399 -> 492 us (28
 // TFLOP/s); attention over the 1511 tokens 505 -> 47 us per layer.  Matrix cores
 // are 31 % busy while a CU has work there: the rest is the start of each launch,
 // whose waves all load first and multiply after.
@@ -60,14 +60,18 @@ CRF_DEV void tile_row(const F32Gemm &p, int tn, int b, int i, int &seg, int &row
 // operands: the k order is permuted the same way on both sides.  With a norm
 // gain the tokens are multiplied by it as they are loaded, their squares are
 // summed alongside (the workgroup sees every k of its tokens), and the row
-// factor 1/rms multiplies the sums at the end.  LORA: the adapter's rank rows
+// factor 1/rms multiplies the sums at the end.  LORA = 1: the adapter's rank rows
 // (rank <= 16) are one more block per target, so U never leaves the workgroup;
-// larger ranks read U from memory (formed by the F32_PLAIN launch).
+// LORA = 2 (rank <= 8): gate's are rows 0-7 and up's rows 8-15 of one block, a
+// sixth of a 4 x 4 tile's products less (1511 tokens, d_ffn = 704: 39.6 -> 34.3
+// us); larger ranks read U from memory (formed
+// by the F32_PLAIN launch).
 // Small tiles (2 x 1 or 2 x 2 blocks, 4 waves) keep a few hundred rows spread
 // over the CUs; big ones (4 x 4 blocks, 2 waves) read half the bytes per FLOP.
-template <int EPI, int FB, int TB, int NW, bool LORA>
+template <int EPI, int FB, int TB, int NW, int LORA>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Gemm p) {
-  constexpr int XB = LORA ? (EPI == F32_SWIGLU ? 2 : 1) : 0;  // adapter blocks
+  constexpr bool PACK = LORA == 2;
+  constexpr int XB = LORA ? (EPI == F32_SWIGLU && !PACK ? 2 : 1) : 0;  // adapter blocks
   constexpr int NB = FB + XB;
   constexpr int UNROLL = FB * TB <= 4 ? 2 : 1;  // k-steps per batch; two batches in flight
   __shared__ f32x4 red[NW][NB * TB][64];
@@ -93,8 +97,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Gemm p) {
   }
 #pragma unroll
   for (int x = 0; x < XB; ++x) {
-    const float *a = p.la[x ? seg1 : seg0];
-    wp[FB + x] = a ? a + (int64_t)min(r16, p.rank - 1) * p.K : wp[0];
+    const float *a = p.la[(PACK ? r16 >= 8 : x > 0) ? seg1 : seg0];
+    wp[FB + x] = a ? a + (int64_t)min(PACK ? r16 % 8 : r16, p.rank - 1) * p.K : wp[0];
   }
   f32x4 acc[NB][TB];
   float ss[TB];
@@ -162,8 +166,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Gemm p) {
       tile_row<EPI, FB>(p, tn, b, r16, seg, row);
       if (LORA && p.lb[seg]) {
         const float *lb = p.lb[seg] + (int64_t)min(row, p.seg_rows[seg] - 1) * p.rank;
+        const int j = PACK ? (kg / 2 == (b >= FB / 2) ? 4 * (kg % 2) : p.rank) : 4 * kg;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lbv[b][i] = 4 * kg + i < p.rank ? lb[4 * kg + i] : 0.f;
+        for (int i = 0; i < 4; ++i) lbv[b][i] = j + i < p.rank ? lb[j + i] : 0.f;
       }
       if (EPI == F32_RESID)
         rin[b] = ldf4(p.resid_in + (int64_t)m1 * p.ldo + min(tn * 16 * FB + 16 * b + 4 * kg, p.seg_rows[0] - 4));
@@ -212,8 +217,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Gemm p) {
 #pragma unroll
         for (int x = 0; x < (EPI == F32_SWIGLU ? 2 : 1); ++x) {
           const int seg = x ? seg1 : seg0;
-          if (LORA) {
-            u[x] = v[FB + (XB > 0 ? x : 0)] * p.scale;
+          if (PACK) {
+            u[x] = kg / 2 == x ? v[FB] * p.scale : ZERO4;
+          } else if (LORA) {
+            u[x] = v[FB + (XB > 1 ? x : 0)] * p.scale;
           } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -459,7 +466,7 @@ int n_tiles(const F32Gemm &p) {
   return (p.seg_rows[0] + per - 1) / per;
 }
 
-template <int EPI, bool LORA>
+template <int EPI, int LORA>
 void go(hipStream_t s, const F32Gemm &p) {
   const int small = n_tiles<EPI, 2>(p) * ((p.M + 31) / 32);
   if (small <= F32_FEW_TILES) {
@@ -485,10 +492,15 @@ hipError_t launch_gemm_f32(hipStream_t s, F32Epi epi, const F32Gemm &p0) {
   if (!any) p.rank = 0;
   const bool fused = p.rank > 0 && p.rank <= F32_FUSED_RANK;
   switch (epi) {
-    case F32_PLAIN: go<F32_PLAIN, false>(s, p); break;
-    case F32_RESID: fused ? go<F32_RESID, true>(s, p) : go<F32_RESID, false>(s, p); break;
-    case F32_SWIGLU: fused ? go<F32_SWIGLU, true>(s, p) : go<F32_SWIGLU, false>(s, p); break;
-    case F32_QKV: fused ? go<F32_QKV, true>(s, p) : go<F32_QKV, false>(s, p); break;
+    case F32_PLAIN: go<F32_PLAIN, 0>(s, p); break;
+    case F32_RESID: fused ? go<F32_RESID, 1>(s, p) : go<F32_RESID, 0>(s, p); break;
+    case F32_SWIGLU:
+      if (fused && p.rank <= 8)
+        go<F32_SWIGLU, 2>(s, p);
+      else
+        fused ? go<F32_SWIGLU, 1>(s, p) : go<F32_SWIGLU, 0>(s, p);
+      break;
+    case F32_QKV: fused ? go<F32_QKV, 1>(s, p) : go<F32_QKV, 0>(s, p); break;
   }
   return hipGetLastError();
 }
