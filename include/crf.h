@@ -126,9 +126,9 @@ int32_t crf_abi_version(void);
  * 0..max_tokens-1.  Besides the per-token buffers (fp32 residual stream,
  * normalised input, queries, attention output, SwiGLU output, LoRA
  * down-projections), a bf16 context holds fixed-size scratch for split
- * work: one 256x256 fp32 tile per compute unit for the K-parts of the QKV and
- * residual GEMMs (64 MiB on 256 CUs), key-split attention partials for
- * decoding steps (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats, and
+ * work: two 256x256 fp32 tiles per compute unit for the K-parts of the QKV and
+ * residual GEMMs (128 MiB on 256 CUs), key-split attention partials
+ * (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats, and
  * at least 512 x 128 x (head_dim+4) when max_tokens >= 2048: 35 MB at most),
  * K-split LoRA partials and, when max_lora_rank > 0, the down projection's
  * adapter sums formed inside the gate/up projection (4 x 2 x 256 x 16 floats
@@ -284,9 +284,8 @@ crf_status crf_layer_drift(crf_context *ctx, const crf_model_dims *dims, const c
  * memory on `stream` (so the call returns once they are copied).  Calls that
  * overlap on one device race on its scratch: serialise them (one stream, or
  * the caller's own ordering).  A request whose tables and partials exceed the
- * scratch (segments: two per adapter target and layer; chunks of 2^13 to 2^16
- * elements each; per segment and per chunk about 16 bytes and 8 for each
- * version) is rejected with
+ * scratch (segments: two per adapter target, layer and version; chunks of 2^16
+ * elements each; about 64 bytes per chunk and segment) is rejected with
  * WORKSPACE before anything is copied or launched.  Errors are reported through
  * crf_last_error(NULL): INVALID_ARG, SHAPE, UNSUPPORTED (as crf_validate_dims),
  * WORKSPACE, HIP. */

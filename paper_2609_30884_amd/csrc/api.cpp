@@ -919,7 +919,7 @@ struct DriftPlan {
   int L = 0, V = 0, chunk = 0;
   size_t n_segs = 0, n_chunks = 0;
   size_t o_segs = 0, o_b = 0, o_chunks = 0, o_first = 0, o_anchor = 0, o_ticket = 0, host_bytes = 0, o_part = 0,
-         o_sq = 0, dev_bytes = 0;
+         o_sq = 0, dev_bytes = 0, stated_bytes = 0;
 };
 
 // Validates a drift request and sizes its tables (touches no device).
@@ -976,6 +976,22 @@ crf_status drift_plan(crf_context *ctx, const crf_model_dims *dims, const crf_lo
         (pl.n_chunks <= DRIFT_MAX_CHUNKS && pl.dev_bytes <= CRF_DRIFT_NOALLOC_MAX_BYTES))
       break;
   }
+  // The size that the no-allocation call's limit is stated in: per version 32
+  // bytes a segment and 24 + 8 a chunk of 2^16 elements, and the tables of the
+  // outputs.  No layout above with its largest chunks takes more.
+  size_t chunks16 = 0;
+  for (int l = 0; l < L; ++l)
+    for (int t = 0; t < CRF_NUM_TARGETS && current[l].rank > 0; ++t) {
+      if (!current[l].A[t]) continue;
+      int d_out, d_in;
+      target_shape(*dims, t, d_out, d_in);
+      for (int64_t cnt : {(int64_t)current[l].rank * d_in, (int64_t)d_out * current[l].rank})
+        chunks16 += (size_t)((cnt + 65535) / 65536);
+    }
+  auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t V = (size_t)n_versions, n_out = V * L;
+  pl.stated_bytes = al(V * pl.n_segs * 32) + al(V * chunks16 * 24) + 2 * al(n_out * sizeof(int)) + al(L * sizeof(int)) +
+                    al((V * chunks16 + 1) * sizeof(double)) + al(n_out * sizeof(double));
   return CRF_OK;
 }
 
@@ -1372,10 +1388,11 @@ crf_status crf_layer_drift_noalloc(const crf_model_dims *dims, const crf_lora_la
   if ((st = drift_plan(nullptr, dims, current, n_versions, versions, anchor_version, drift_out, risk_out, pl)) !=
       CRF_OK)
     return st;
-  if (pl.dev_bytes > CRF_DRIFT_NOALLOC_MAX_BYTES)
+  const size_t need = std::max(pl.stated_bytes, pl.dev_bytes);
+  if (need > CRF_DRIFT_NOALLOC_MAX_BYTES)
     return fail(nullptr, CRF_ERR_WORKSPACE,
-                "crf_layer_drift_noalloc: %zu segments in %zu chunks need %zu bytes of scratch, more than its %d",
-                pl.n_segs, pl.n_chunks, pl.dev_bytes, CRF_DRIFT_NOALLOC_MAX_BYTES);
+                "crf_layer_drift_noalloc: %zu segments of %d versions need %zu bytes of scratch, more than its %d",
+                pl.n_segs, pl.V, need, CRF_DRIFT_NOALLOC_MAX_BYTES);
   void *scratch = nullptr;
   hipError_t e = drift_noalloc_scratch(&scratch);
   if (e != hipSuccess)
