@@ -126,8 +126,9 @@ int32_t crf_abi_version(void);
  * 0..max_tokens-1.  Besides the per-token buffers (fp32 residual stream,
  * normalised input, queries, attention output, SwiGLU output, LoRA
  * down-projections), a bf16 context holds fixed-size scratch for split
- * work: two 256x256 fp32 tiles per compute unit for the K-parts of the QKV and
- * residual GEMMs (128 MiB on 256 CUs), key-split attention partials
+ * work: one or, for prefixes of more 256x256 tiles of d_model than half the
+ * compute units, two such fp32 tiles per compute unit for the K-parts of the QKV
+ * and residual GEMMs (64 or 128 MiB on 256 CUs), key-split attention partials
  * (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats, and
  * at least 512 x 128 x (head_dim+4) when max_tokens >= 2048: 35 MB at most),
  * K-split LoRA partials and, when max_lora_rank > 0, the down projection's

@@ -58,9 +58,9 @@ struct crf_context {
   float *lora_part = nullptr;  // bf16 path, <= 16 token rows: parts of the LoRA down-projections
   int64_t lora_part_floats = 0;
   // bf16 path: K-part partials of the projections (gemm_part_floats), of which
-  // the 256x256 tiles' last round may fill twice as many
+  // the 256x256 tiles' last round may fill more (gemm_split_floats)
   float *gemm_part = nullptr;
-  int64_t gemm_part_floats = 0;
+  int64_t gemm_part_floats = 0, gemm_split_floats = 0;
   float *dn_part = nullptr;    // bf16 path: down-projection adapter sums fused into gate/up
   int *dn_head = nullptr;      //   and the table of their first tiles
   unsigned *tickets = nullptr; // bf16 path: arrival counters of K-split workgroups, zero between launches
@@ -628,7 +628,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       p.q_scale = attn_query_scale(hd);
       p.pos0 = pos0;
       p.split_part = ctx->gemm_part;
-      p.split_cap = ctx->in_batch ? ctx->gemm_part_floats : 2 * ctx->gemm_part_floats;
+      p.split_cap = ctx->in_batch ? ctx->gemm_part_floats : ctx->gemm_split_floats;
       p.n_cu = ctx->n_cu;
       return p;
     };
@@ -1145,16 +1145,19 @@ crf_status crf_context_create(const crf_model_dims *dims, int32_t max_tokens, in
     ctx->lora_part_floats =
         (int64_t)std::max<size_t>((std::max({D, f, dq}) + 255) / 256, dims->n_q_heads) * 16 * 3 * ctx->rank_pad;
     if ((st = dmalloc(ctx, &ctx->lora_part, (size_t)ctx->lora_part_floats * 4)) != CRF_OK) return cleanup(st);
-    // one 256x256 fp32 partial per compute unit, and a second for K-parts in two rounds
+    // one 256x256 fp32 partial per compute unit, and a second for K-parts in two
+    // rounds where a down projection can have more tiles than half the units
     if (hipDeviceGetAttribute(&ctx->n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
       ctx->n_cu = 0;
     ctx->gemm_part_floats = (int64_t)std::max(ctx->n_cu, 0) * 256 * 256;
+    ctx->gemm_split_floats =
+        ctx->gemm_part_floats * (2 * ((T + 255) / 256) * ((D + 255) / 256) > (size_t)std::max(ctx->n_cu, 0) ? 2 : 1);
     ctx->n_tickets = 512;
     if ((st = dmalloc(ctx, &ctx->tickets, ctx->n_tickets * sizeof(unsigned))) != CRF_OK) return cleanup(st);
     if (hipMemset(ctx->tickets, 0, ctx->n_tickets * sizeof(unsigned)) != hipSuccess)
       return cleanup(fail(ctx, CRF_ERR_HIP, "context init: hipMemset"));
     if (ctx->gemm_part_floats > 0 &&
-        (st = dmalloc(ctx, &ctx->gemm_part, (size_t)ctx->gemm_part_floats * 2 * 4)) != CRF_OK)
+        (st = dmalloc(ctx, &ctx->gemm_part, (size_t)ctx->gemm_split_floats * 4)) != CRF_OK)
       return cleanup(st);
     // fused down-projection adapter sums: DN_RUNS runs of [2][256][16] per
     // compute unit, and one table entry per gate/up tile
