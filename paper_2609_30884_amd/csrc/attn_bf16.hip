@@ -193,6 +193,14 @@ inline int attn_halves_grid(int nq, int nkv, int nqb, int xcd_r, int long0) {
   return 8 * (nq / nkv) * ((nqb + xcd_r - 1) / xcd_r + (nqb - long0 + xcd_r - 1) / xcd_r);
 }
 
+// Logical pages that a query block whose last query sits at `last_key` may load
+// from: it loads whole tiles, of which the last can run on past last_key, over
+// the keys of the block's successors, up to the M keys there are.
+__host__ __device__ inline int attn_pages(int last_key, int M, int ps) {
+  const int end = (last_key / BKV + 1) * BKV;
+  return ((end < M ? end : M) - 1) / ps + 1;
+}
+
 // PS: page size when fixed at compile time (16), 0 = runtime kv.page_size.
 template <int HD, int PS>
 __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__restrict__ Q, PagedKV kv,
@@ -268,7 +276,7 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
     t_begin = split * split_tiles;
     t_end = min(ntiles, t_begin + split_tiles);
   }
-  const int n_pages_needed = last_key / ps + 1;
+  const int n_pages_needed = attn_pages(last_key, M, ps);
 
   // pgbase[i] = base of logical page pg_first + i; refilled only between barriers.
   int pg_first = 0;
@@ -470,10 +478,12 @@ __global__ __launch_bounds__(NT, 8 / NW) void attn_bf16_kernel(const bf16 *__res
     }
   };
 
-  fill_pages(t_begin * BKV / ps);
-  __syncthreads();
-  dma(t_begin * BKV, ks0, vs0);
-  tile(t_begin, ks0, vs0, ks1, vs1, std::true_type());
+  if (t_begin < t_end) {  // (a part past the block's last key loads nothing)
+    fill_pages(t_begin * BKV / ps);
+    __syncthreads();
+    dma(t_begin * BKV, ks0, vs0);
+    tile(t_begin, ks0, vs0, ks1, vs1, std::true_type());
+  }
   for (int it = t_begin + 1; it < t_end; it += 2) {
     tile(it, ks1, vs1, ks0, vs0, std::false_type());
     if (it + 1 < t_end) tile(it + 1, ks0, vs0, ks1, vs1, std::false_type());

@@ -6,8 +6,10 @@ reordering, the per-XCD remap) over the window projections of the 1.5B and
 7B shapes, ragged shapes and 200 seeded random ones, at several compute-unit
 counts and partial-buffer capacities: every (tile, K slice) pair must be
 computed by exactly one item.  tests/native/attn_schedule_check.cpp does the
-same for attention's workgroup -> (query head, query block) map.  Both are
-compiled with hipcc against the kernel sources and run on the host.
+same for attention's workgroup -> (query head, query block) map, and
+tests/native/attn_pages_check.cpp checks that a workgroup stages the base of
+every page its tiles load.  All are compiled with hipcc against the kernel
+sources and run on the host.
 """
 import os
 import shutil
@@ -41,3 +43,7 @@ def test_gemm_schedule_computes_every_tile_slice_once(tmp_path):
 
 def test_attention_serves_every_head_and_query_block_once(tmp_path):
     assert _build_and_run(tmp_path, "attn_schedule_check") > 2600
+
+
+def test_attention_stages_every_page_it_loads(tmp_path):
+    assert _build_and_run(tmp_path, "attn_pages_check") > 1200
