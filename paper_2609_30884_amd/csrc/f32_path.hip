@@ -321,7 +321,10 @@ constexpr int AW = 8;  // waves per attention workgroup
 // through LDS.  S^T = K Q^T (keys on MFMA rows) leaves a lane with 4 keys of
 // one query, which is the token operand of O^T = V^T P^T as it stands; the V
 // rows are taken in an order that lets a lane load 4 consecutive values.
-// Keys on a rejected page count as zero keys and values.
+// Keys on a rejected page count as zero keys and values.  A key that some of the
+// block's queries do not see has probability 0 there, and 0 times a non-finite
+// value would be NaN: where a tile on the diagonal holds such a value, its keys
+// past the first query are added by a loop of their own, for those that see them.
 template <int HD>
 __global__ __launch_bounds__(64 * AW) void attn_f32_kernel(const float *__restrict__ Q, PagedKV kv,
                                                        float *__restrict__ O, int M, int nq, int nkv) {
@@ -401,6 +404,19 @@ __global__ __launch_bounds__(64 * AW) void attn_f32_kernel(const float *__restri
       }
     mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    bool apart = false;  // (uniform) keys past q0 are added apart
+    if (k0 + 31 > q0) {
+      float z = 0.f;  // NaN where a value is not finite
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int c = 0; c < VC; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = fmaf(vok[b][i] ? vf[b][i][c][e] : 0.f, 0.f, z);
+      apart = __builtin_amdgcn_ballot_w64(!(z == 0.f)) != 0;
+    }
     const float mn = fmaxf(m, mt);
     const float ref = mn == -INFINITY ? 0.f : mn;  // no key of this wave seen yet
     const float alpha = expf(m - ref);
@@ -416,10 +432,26 @@ __global__ __launch_bounds__(64 * AW) void attn_f32_kernel(const float *__restri
       for (int i = 0; i < 4; ++i) {
         const float pr = expf(s[b][i] - ref);
         l += pr;
+        const bool in = vok[b][i] && !(apart && k0 + 16 * b + 4 * kg + i > q0);
 #pragma unroll
         for (int c = 0; c < VC; ++c)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[c][e] = mfma_f32(vok[b][i] ? vf[b][i][c][e] : 0.f, pr, o[c][e]);
+          for (int e = 0; e < 4; ++e) o[c][e] = mfma_f32(in ? vf[b][i][c][e] : 0.f, pr, o[c][e]);
+        if (apart)
+          for (int g = 0; g < 4; ++g) {
+            const int key = k0 + 16 * b + 4 * g + i;
+            const float pk = __shfl(pr, 16 * g + r16, 64);
+            const int64_t r = __shfl(krow[b], 4 * g + i, 64);
+            if (key <= q0 || key > qi || r < 0) continue;
+#pragma unroll
+            for (int c = 0; c < VC; ++c)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) {
+                const f32x4 x = ldf4(V + r + 64 * c + 16 * kg + 4 * j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[c][e][j] = fmaf(pk, x[e], o[c][e][j]);
+              }
+          }
       }
 #pragma unroll
     for (int b = 0; b < 2; ++b) krow[b] = nrow[b];
