@@ -217,10 +217,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const F32Gemm p) {
 #pragma unroll
         for (int x = 0; x < (EPI == F32_SWIGLU ? 2 : 1); ++x) {
           const int seg = x ? seg1 : seg0;
-          if (PACK) {
-            u[x] = kg / 2 == x ? v[FB] * p.scale : ZERO4;
-          } else if (LORA) {
-            u[x] = v[FB + (XB > 1 ? x : 0)] * p.scale;
+          if (LORA) {  // (rows past the rank, and PACK's other target, take no part: 0 times an infinity would)
+            const bool own = !PACK || kg / 2 == x;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              u[x][i] = own && 4 * (PACK ? kg % 2 : kg) + i < p.rank ? v[FB + (XB > 1 ? x : 0)][i] * p.scale : 0.f;
           } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

@@ -39,3 +39,20 @@ def test_non_finite_token_leaves_earlier_tokens_alone(n, t, page, hd):
         assert rel_to_rms(g[:t], r[:t]) <= TOL["f32"]
         assert (g[:t // 16 * 16] == r[:t // 16 * 16]).all()
     assert not torch.isfinite(case.hidden_out[t:]).any(dim=1).any()   # every later token sees it
+
+
+# ranks that leave rows of the adapter's 16-row block unused, and one that fills it
+@pytest.mark.parametrize("rank", [1, 3, 13, 16])
+def test_infinite_adapter_input_stays_infinite(rank):
+    """U of the last rank row overflows to +Inf and its factor is positive: V is
+    +Inf, not the NaN of an unused row's zero factor times that U."""
+    print(f"[case] f32 infinite U, rank {rank}", flush=True)
+    case = _case(20, 16, rank=rank, targets=("v",))
+    case.hidden_dev.fill_(1.0)
+    a, b = case.lora_dev[0]["targets"]["v"]
+    a[rank - 1] = 3e38
+    b[:, rank - 1] = 0.5
+    run_gpu_window(case, h=1, hidden_out=False)
+    torch.cuda.synchronize()
+    k, v = gpu_kv(case, 0)
+    assert (v == float("inf")).all()
