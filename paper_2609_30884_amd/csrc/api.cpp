@@ -854,6 +854,7 @@ crf_status run_layers_f32(crf_context *ctx, const void *hb, const crf_layer_weig
       p.seg1 = kv_only ? 0 : dq;
       p.seg2 = p.seg1 + dkv;
       p.N = p.seg2 + dkv;
+      p.n_form = dq + 2 * dkv;
       if (kv_only) p.la[0] = p.lb[0] = nullptr;
       p.out = q;
       p.ldo = dq;

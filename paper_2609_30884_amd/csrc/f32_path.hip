@@ -499,9 +499,13 @@ int n_tiles(const F32Gemm &p) {
   return (p.seg_rows[0] + per - 1) / per;
 }
 
+// (A QKV launch without Q takes the form that it would take with Q: the forms
+// split K over four waves or two, and K and V are the same to the bit either way.)
 template <int EPI, int LORA>
 void go(hipStream_t s, const F32Gemm &p) {
-  const int small = n_tiles<EPI, 2>(p) * ((p.M + 31) / 32);
+  F32Gemm whole = p;
+  if (EPI == F32_QKV) whole.N = p.n_form;
+  const int small = n_tiles<EPI, 2>(whole) * ((p.M + 31) / 32);
   if (small <= F32_FEW_TILES) {
     hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 1, 4, LORA>), dim3(n_tiles<EPI, 2>(p), (p.M + 15) / 16), dim3(256), 0,
                        s, p);

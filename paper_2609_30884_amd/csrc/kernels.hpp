@@ -34,6 +34,7 @@ struct F32Gemm {
   const float *w[3];       // [seg_rows, K]
   int seg_rows[3];
   int seg1, seg2;
+  int n_form;              // F32_QKV: rows with Q's, whether the launch has them or not
   // adapter of segment s: la [rank, K], lb [seg_rows, rank] (both null: none);
   // past F32_FUSED_RANK U [M, ldu] holds segment s's scaled U at column s * rank
   const float *la[3], *lb[3];

@@ -47,7 +47,7 @@ def test_f32_tile_edges(name):
     assert_window_parity(case, out, kv, label=f"f32 {name}")
 
 
-@pytest.mark.parametrize("name", ["n17_r17", "big_gateup_r8"])
+@pytest.mark.parametrize("name", ["n17_r17", "big_gateup_r8", "big_all_r33"])
 def test_f32_window_without_hidden_out_writes_the_same_cache(name):
     case = _case(name)
     run_gpu_window(case)
