@@ -142,12 +142,15 @@ inline int attn_window_grid(int nq, int nkv, int nqb, int &xcd_r) {
 // Query head, query block and key split of workgroup `bid` of a key-split
 // launch; false for padding.  A unit is one split of one KV head: its workgroups
 // (every query block of the group's heads, or one when packed) read the same
-// K/V tiles, so they run on one XCD, units taking the XCDs in turn.
+// K/V tiles.  The XCDs share the list of all units' workgroups evenly, each
+// taking a run of it, so that none idles however few the units are and a unit's
+// workgroups lie on as few XCDs as that allows.
 __host__ __device__ inline bool attn_split_block(int bid, int nq, int nkv, int nqb, int n_splits, int packed,
                                                  int &head, int &qblk, int &split) {
   const int group = nq / nkv, per = packed ? 1 : group * nqb;
-  const int j = bid / 8, u = bid % 8 + 8 * (j / per), w = j % per;
-  if (u >= nkv * n_splits) return false;
+  const int n = nkv * n_splits * per, x = bid % 8, j = bid / 8;
+  if (j >= n / 8 + (x < n % 8)) return false;
+  const int i = x * (n / 8) + (x < n % 8 ? x : n % 8) + j, u = i / per, w = i % per;
   split = u / nkv;
   attn_block(packed ? u % nkv : 0, nq, nkv, nqb, 0, packed, head, qblk);
   if (!packed) {
@@ -158,7 +161,7 @@ __host__ __device__ inline bool attn_split_block(int bid, int nq, int nkv, int n
 }
 
 inline int attn_split_grid(int nq, int nkv, int nqb, int n_splits, int packed) {
-  return 8 * ((nkv * n_splits + 7) / 8) * (packed ? 1 : nq / nkv * nqb);
+  return 8 * ((nkv * n_splits * (packed ? 1 : nq / nkv * nqb) + 7) / 8);
 }
 
 // Window launch whose query blocks from `long0` on have their keys in two parts
@@ -650,28 +653,45 @@ inline int attn_halves(int Mq, int q_off, int nq, int nqb, int hd, int64_t part_
   return -1;
 }
 
+// Tiles of keys per split of a launch whose keys are split over workgroups (0:
+// none), for room of max_splits partials of every row.
+//   A few query rows (<= 16): when the group's heads fit one tile (packed), one
+// workgroup serves all of them, so the K/V tiles are read once per KV head.
+//   A few query blocks (the new tokens of a decoding step over a long prefix)
+// leave most of the GPU idle: split until every slot has a workgroup.  Every row
+// is then written as partials and merged, which only pays where every block has
+// the prefix to share out, from a prefix of twice the new tokens on.  Four-layer
+// steps, whole against split: 12/2 heads of 64, 2000 + 400 tokens 302 -> 292 us
+// and 4000 + 300 338 -> 296, but 1500 + 800 355 -> 367 and 1000 + 2000 502 -> 599;
+// 16/2 heads of 128, 2000 + 1500 tokens 1289 -> 1371.  A window has no prefix
+// (one layer of 1.5B shapes over 2048 / 2688 tokens 329 -> 360 / 419 -> 451 us;
+// its long blocks are attn_halves' business).
+inline int attn_split(int Mq, int q_off, int nq, int nkv, int64_t max_splits, int &packed) {
+  const int nqb = (Mq + BQ - 1) / BQ, ntiles = (q_off + Mq + BKV - 1) / BKV;
+  packed = 0;
+  if (max_splits < 2) return 0;
+  if (Mq <= 16 && ntiles >= 8) {
+    packed = (nq / nkv) * Mq <= BQ;
+    const int units = packed ? nkv : nq;
+    return std::max<int>(std::max<int>(1, (ntiles * units + SPLIT_WG - 1) / SPLIT_WG),
+                         (int)((ntiles + max_splits - 1) / max_splits));
+  }
+  if (Mq > 16 && q_off >= 2 * (int64_t)Mq && nq * nqb * 2 <= ATTN_SLOTS && ntiles >= 32) {
+    const int sp = std::min<int>(ATTN_SLOTS / (nq * nqb), (int)std::min<int64_t>(max_splits, ntiles / 8));
+    if (sp >= 2) return (ntiles + sp - 1) / sp;
+  }
+  return 0;
+}
+
 template <int HD>
 void launch(hipStream_t s, const bf16 *Q, const PagedKV &kv, bf16 *O, int Mq, int q_off, int nq, int nkv,
             uint32_t pool_bytes, float *part, int64_t part_floats, AttnLora *lora) {
   const int nqb = (Mq + BQ - 1) / BQ;
-  int xcd_r = 0, grid = nqb * nq, n_splits = 1, split_tiles = 0, packed = 0, long0 = -1;
+  int xcd_r = 0, grid = nqb * nq, n_splits = 1, packed = 0, long0 = -1;
   const int64_t keys = (int64_t)q_off + Mq;
   const int ntiles = (int)((keys + BKV - 1) / BKV);
   const int64_t max_splits = part ? part_floats / ((int64_t)nq * Mq * (HD + 4)) : 0;
-  if (Mq <= 16 && ntiles >= 8 && max_splits >= 2) {
-    // a few query rows over a long prefix: split the keys over workgroups;
-    // when the group's heads fit one tile, one workgroup serves all of them
-    // (the K/V tiles are read once per KV head)
-    packed = (nq / nkv) * Mq <= BQ;
-    const int units = packed ? nkv : nq;
-    split_tiles = std::max<int>(1, (ntiles * units + SPLIT_WG - 1) / SPLIT_WG);
-    split_tiles = std::max<int>(split_tiles, (int)((ntiles + max_splits - 1) / max_splits));
-  } else if (nq * nqb * 2 <= ATTN_SLOTS && ntiles >= 32 && max_splits >= 2) {
-    // a few query blocks (the new tokens of a decoding step over a long prefix)
-    // leave most of the GPU idle: split the keys until every slot has a workgroup
-    int sp = std::min<int>(ATTN_SLOTS / (nq * nqb), (int)std::min<int64_t>(max_splits, ntiles / 8));
-    if (sp >= 2) split_tiles = (ntiles + sp - 1) / sp;
-  }
+  int split_tiles = attn_split(Mq, q_off, nq, nkv, max_splits, packed);
   if (split_tiles > 0) {
     n_splits = (ntiles + split_tiles - 1) / split_tiles;
     grid = attn_split_grid(nq, nkv, nqb, n_splits, packed);

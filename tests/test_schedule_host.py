@@ -8,7 +8,8 @@ counts and partial-buffer capacities: every (tile, K slice) pair must be
 computed by exactly one item.  tests/native/attn_schedule_check.cpp does the
 same for attention's workgroup -> (query head, query block) map, and
 tests/native/attn_pages_check.cpp checks that a workgroup stages the base of
-every page its tiles load.  All are compiled with hipcc against the kernel
+every page its tiles load, and tests/native/attn_split_check.cpp that a key-split
+launch serves every part once and loads the XCDs evenly.  All are compiled with hipcc against the kernel
 sources and run on the host.
 """
 import os
@@ -47,3 +48,7 @@ def test_attention_serves_every_head_and_query_block_once(tmp_path):
 
 def test_attention_stages_every_page_it_loads(tmp_path):
     assert _build_and_run(tmp_path, "attn_pages_check") > 1200
+
+
+def test_key_splits_load_the_xcds_evenly(tmp_path):
+    assert _build_and_run(tmp_path, "attn_split_check") > 10000
