@@ -222,8 +222,9 @@ typedef struct {
  * layer's whole n_pages*page_stride span, since the pages are chosen by the
  * device-side block table) and its hidden_out, and reads those pool spans,
  * its hidden_at_boundary and its block table.  Items with h == 0 or no tokens
- * take part in no conflict.  Results are the same either way (each item's
- * arithmetic does not depend on the lane).
+ * take part in no conflict.  Results are the same either way, and to the bit
+ * those of the items' windows as separate calls on this context (each item's
+ * arithmetic depends on the item alone).
  * Errors: as crf_recompute_window; the failing item's index is in the message;
  * WORKSPACE if the second workspace cannot be allocated. */
 crf_status crf_recompute_window_batched(crf_context *ctx, const crf_model_dims *dims,

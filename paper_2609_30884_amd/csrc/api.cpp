@@ -77,9 +77,6 @@ struct crf_context {
   // the same shape, made by the first such call) and two lane streams forked
   // from the caller's stream
   crf_context *lane2 = nullptr;
-  // an item of a batch of several: what idles in one item's launches another's
-  // use, so work is not split further at the price of partials
-  bool in_batch = false;
   hipStream_t lane_s[2] = {nullptr, nullptr};
   hipEvent_t fork_ev = nullptr, join_ev[2] = {nullptr, nullptr};
 };
@@ -628,7 +625,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
       p.q_scale = attn_query_scale(hd);
       p.pos0 = pos0;
       p.split_part = ctx->gemm_part;
-      p.split_cap = ctx->in_batch ? ctx->gemm_part_floats : ctx->gemm_split_floats;
+      p.split_cap = ctx->gemm_split_floats;
       p.n_cu = ctx->n_cu;
       return p;
     };
@@ -719,7 +716,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
     }
     LAUNCH(ctx, s, CRF_KK_ATTN,
            launch_attn_bf16(s, q, layer_kv(ctx, kv, l), attn, M, pos0, d.n_q_heads, d.n_kv_heads, hd,
-                            ctx->in_batch ? nullptr : ctx->attn_part, ctx->attn_part_floats));
+                            ctx->attn_part, ctx->attn_part_floats));
     any = lora_targets({CRF_O}, tg);
     if (any) LAUNCH(ctx, s, CRF_KK_LORA_DOWN, lora_down(attn, dq, 1));
     {
@@ -1209,13 +1206,6 @@ crf_status crf_recompute_window_batched(crf_context *ctx, const crf_model_dims *
   // run on two lanes, each a stream with its own workspace, so that small
   // windows fill the GPU together; every item's arithmetic is the same either
   // way.  While event timing is on they run in order on `stream`.
-  // (Eight ragged caches of 1.5B shapes: 16.19 ms with the last rounds in three
-  // K-parts and attention's long blocks in two, 16.00 without.)
-  struct InBatch {
-    crf_context *c;
-    ~InBatch() { c->in_batch = false; }
-  } in_batch{ctx};
-  ctx->in_batch = n_items >= 2;
   bool lanes = n_items >= 2 && ctx->timer.mask == 0;
   // Byte ranges each item may write (its window's layers of both pools, its
   // output state) and read (the same pool layers, its boundary state, its
@@ -1264,7 +1254,6 @@ crf_status crf_recompute_window_batched(crf_context *ctx, const crf_model_dims *
       crf_context *c2 = nullptr;
       if (crf_context_create(&ctx->dims, ctx->max_tokens, ctx->max_rank, &c2) != CRF_OK)
         return fail(ctx, CRF_ERR_WORKSPACE, "second workspace for concurrent batch items: %s", g_last_error.c_str());
-      c2->in_batch = true;  // (it runs nothing else)
       ctx->lane2 = c2;
     }
     for (int i = 0; i < 2; ++i) {
