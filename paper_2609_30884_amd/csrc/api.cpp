@@ -430,17 +430,40 @@ crf_status run_layers_mid(crf_context *ctx, const void *hb, const crf_layer_weig
   return CRF_OK;
 }
 
-// Whether a run of `rows` token rows takes the kernels above: while its gate/up
-// projection has at most two rounds of 256x256 tiles, with whole rounds of which
-// the large tiles win (two layers of 1.5B shapes: 1600 tokens 534 against 576
-// us, 2048 tokens 778 against 769; of 7B shapes: 700 tokens 1025 against 1020,
-// 1024 tokens 1320 against 1273).
-bool mid_rows(const crf_context *ctx, int rows) {
+// Whether layers [l0, l0 + h) over `rows` token rows take the kernels above.
+// They save a layer about 45 us of launches, and nothing is paid for tokens that
+// fill a 256-row tile's last half; a row costs more in them for its products (the
+// smaller tiles), for the fp32 K-parts of its Q, K, V, O and down columns, and for
+// the adapters' deltas, which the reductions form on the vector units.  The
+// weights of the four are fitted to 800 windows of nine shapes (100 to 10000
+// tokens, ranks 8 to 64 on none to all targets), each timed on both routes; the
+// faster one is missed by 0.4 % on average.  These kernels against the large
+// tiles: 1.5B shapes, rank 64 on all, one layer, 1536 tokens 367 / 377 us, 1792
+// tokens 423 / 387; 7B shapes, rank 16 on q, k, v, o, two layers, 640 tokens 835 /
+// 861, 700 tokens 907 / 888; d = 768, d_ffn = 2048, rank 64 on all, one layer, 2500
+// tokens 220 / 228, 8192 tokens 593 / 430.
+// Past two rounds of 256x256 gate/up tiles the large tiles' whole rounds win.
+bool mid_rows(const crf_context *ctx, int rows, const crf_lora_layer *lora, int l0, int h) {
   const crf_model_dims &d = ctx->dims;
   if (rows <= 16 || d.d_model > MID_MAX_COLS || ctx->n_cu <= 0) return false;
-  const int64_t tiles = (int64_t)((rows + 255) / 256) * ((2 * d.d_ffn + 255) / 256);
-  const int64_t cols = std::max<int64_t>(dq_of(d) + 2 * dkv_of(d), d.d_model) + 3 * ctx->max_rank;
-  return tiles <= 2 * ctx->n_cu && rows * cols <= ctx->gemm_part_floats;
+  const int64_t D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn;
+  const int64_t tiles = (int64_t)((rows + 255) / 256) * ((2 * f + 255) / 256);
+  const int64_t cols = std::max<int64_t>(dq + 2 * dkv, D) + 3 * ctx->max_rank;
+  if (tiles > 2 * ctx->n_cu || rows * cols > ctx->gemm_part_floats) return false;
+  int64_t delta = 0;  // products of a row's adapter deltas formed by the reductions
+  for (int l = l0; l < l0 + h; ++l) {
+    int64_t n = 0;
+    for (int t : {CRF_Q, CRF_K, CRF_V, CRF_O, CRF_DOWN}) {
+      int d_out, d_in;
+      target_shape(d, t, d_out, d_in);
+      if (has_lora(lora, l, t)) n += (int64_t)lora[l].rank * d_out;
+    }
+    delta = std::max(delta, n);
+  }
+  const int64_t spared = (rows + 255) / 256 * 256 - (rows + 127) / 128 * 128;
+  const double products = (double)(D * (2 * dq + 2 * dkv) + 3 * D * f);
+  return products * (2.8e-4 * rows - 6.1e-4 * (double)spared) +
+             (1.5 * (double)(dq + 2 * dkv + 2 * D) + 0.036 * (double)delta) * rows < 45e6;
 }
 
 // Last gate/up panels (256 weight rows: 128 features) of `rows` tokens that
@@ -588,7 +611,7 @@ crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_wei
                            const crf_lora_layer *lora, int l0, int h, const crf_kv_cache *kv, void *hout,
                            hipStream_t s, int rows, int pos0, bool kv_tail) {
   if (rows <= 16) return run_layers_few(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
-  if (mid_rows(ctx, rows)) return run_layers_mid(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
+  if (mid_rows(ctx, rows, lora, l0, h)) return run_layers_mid(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
   const crf_model_dims &d = ctx->dims;
   const int M = rows, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
   const int rp = ctx->rank_pad, ldu = 3 * rp;

@@ -33,6 +33,9 @@ CASES = {
     "n513_r48": (513, S128, 48, ALL),
     "n40_wide": (40, WIDE, 16, ALL),
     "n512_tall": (512, TALL, 16, ("up", "down")),
+    # two layers on either side of the line that the adapters' deltas draw (rank 64 on all)
+    "n2900_r64": (2900, S64, 64, ALL),
+    "n4400_r64": (4400, S64, 64, ALL),
     "n513_tall": (513, TALL, 16, ("up", "down")),
 }
 
