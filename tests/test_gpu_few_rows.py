@@ -23,6 +23,8 @@ WINDOWS = {
     "n2_r40": (2, S128, 40, ALL),
     "n7_r8_vod": (7, S64, 8, ("v", "o", "down")),
     "n16_r64": (16, S128, 64, ALL),
+    "n4_none": (4, S128, 16, ()),
+    "n5_none": (5, S128, 16, ()),
     "n13_none": (13, S64, 16, ()),
     "n5_r24_kg": (5, S128, 24, ("k", "gate")),
 }
