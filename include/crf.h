@@ -129,9 +129,9 @@ int32_t crf_abi_version(void);
  * work: one or, for prefixes of more 256x256 tiles of d_model than half the
  * compute units, two such fp32 tiles per compute unit for the K-parts of the QKV
  * and residual GEMMs (64 or 128 MiB on 256 CUs), key-split attention partials
- * (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats, and
- * at least 512 x 128 x (head_dim+4) when max_tokens >= 2048: 35 MB at most),
- * K-split LoRA partials and, when max_lora_rank > 0, the down projection's
+ * (ceil(max_tokens/64) x n_q_heads x 16 x (head_dim+4) floats, 61 MB for 16384
+ * tokens of 28 heads of 128; from max_tokens = 2048 on at least 512 x 128 x
+ * (head_dim+4), 35 MB at head_dim 128), K-split LoRA partials and, when max_lora_rank > 0, the down projection's
  * adapter sums formed inside the gate/up projection (4 x 2 x 256 x 16 floats
  * per compute unit, 32 MiB on 256 CUs, plus one int per gate/up tile), and 2 KiB
  * of arrival counters.  All of
@@ -187,7 +187,10 @@ crf_status crf_validate_window(const crf_model_dims *dims, int32_t l0, int32_t h
  *                 (supplementary Eq. sup-layer-cache-dependency:
  *                 C_l = G_l(H_{l-1})), so it runs RMSNorm and the K/V
  *                 projections (LoRA, bias, rotary, page write) only.
- *                 The K/V written are the same either way.
+ *                 The K/V written are the same either way: to the bit in an
+ *                 fp32 context, in a bf16 one up to the order in which a
+ *                 projection's products are summed (which follows from how
+ *                 many rows are projected together).
  * h == 0 is direct reuse: nothing is launched and hidden_out (if given and
  * distinct) is not written.  Layers outside the window and pages outside the
  * block table are never touched.  n_tokens comes from kv_cache->n_tokens and

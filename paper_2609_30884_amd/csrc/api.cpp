@@ -53,7 +53,7 @@ struct crf_context {
   void *u = nullptr;       // bf16: [T, 3*rank_pad] LoRA down-projections; fp32: [T, 3*max_rank] past the fused ranks
   float2 *rope_cs = nullptr;
   int *d_err = nullptr;
-  float *attn_part = nullptr;  // bf16 path, <= 16 query rows: key-split attention partials
+  float *attn_part = nullptr;  // bf16 path: key-split attention partials
   int64_t attn_part_floats = 0;
   float *lora_part = nullptr;  // bf16 path, <= 16 token rows: parts of the LoRA down-projections
   int64_t lora_part_floats = 0;
@@ -471,7 +471,12 @@ bool mid_rows(const crf_context *ctx, int rows, const crf_lora_layer *lora, int 
 // rounds, while they fill at most half a round of large tiles, i.e. one round of
 // the small ones at two to a CU: 30 us instead of a round of 48 at 1.5B shapes
 // and 4096 tokens (96 tiles of 1120); 7B shapes, 777 tokens, 80 tiles of 592 and
-// the padding of the last token tile: 285 -> 252 us.
+// the padding of the last token tile: 285 -> 252 us.  Whole windows of seven
+// shapes with the tail against without: 1 to 5 % faster after up to four rounds
+// however full the last is (two layers of 1.5B shapes, 2304 tokens, 126 tiles: 746
+// -> 720 us; 7B shapes, 1536 tokens, 120 tiles: 1571 -> 1531), after more between
+// 3 % faster and 2 % slower, without a line between them (7B shapes, 5888 tokens,
+// 92 tiles: 5681 -> 5514 us; 4608 tokens, 108 tiles: 4165 -> 4235).
 int gate_up_tail(const crf_context *ctx, int rows) {
   const int tiles_m = (rows + 255) / 256, tiles_n = (2 * ctx->dims.d_ffn + 255) / 256;
   if (ctx->n_cu <= 0 || (int64_t)tiles_m * tiles_n <= ctx->n_cu) return 0;

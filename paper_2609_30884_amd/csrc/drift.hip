@@ -6,8 +6,10 @@
 // current adapter once for four versions, 16 bytes per lane and four loads per
 // tensor ahead of the sums, and the workgroup that finishes last forms the
 // outputs, so that there is no second launch.  Measured: 28 layers x 4 versions at 1.5B shapes
-// (44 MB) 32 + 5 -> 20 us on the GPU, 56 -> 25 us a call; x 2 versions at 7B
-// shapes (242 MB) 85 + 8 -> 51 us (4.7 TB/s), 153 -> 66 us a call.  The first
+// (44 MB) 32 + 5 -> 20 us on the GPU, 57 -> 26 us a call; x 2 versions at 7B
+// shapes (242 MB) 85 + 8 -> 51 us (4.7 TB/s), 153 -> 71 us a call, issued one after
+// another (each waited for: 69 -> 48 and 165 -> 84 us; the first on new adapters 217
+// -> 164 and 170 -> 127).  The first
 // is all latency: tables, chunk, and the last workgroup's two rounds of loads.
 #include <math.h>
 

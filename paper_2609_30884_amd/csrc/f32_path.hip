@@ -9,8 +9,8 @@
 // gate/up, down) where one kernel per operation took 20; every launch splits K
 // over the waves of a workgroup so that its chain of loads stays short.
 // Measured: 2 layers of d = 256 over 128 tokens (rank 8 on q, k, v, o) 966 ->
-// 66 us, 4 layers over 1511 tokens (rank 8 on all seven) 4399 -> 492 us (28
-// TFLOP/s); attention over the 1511 tokens 505 -> 47 us per layer.  Matrix cores
+// 66 us, 4 layers over 1511 tokens (rank 8 on all seven) 4399 -> 473 us (30
+// TFLOP/s); attention over the 1511 tokens 505 -> 42 us per layer.  Matrix cores
 // are 31 % busy while a CU has work there: the rest is the start of each launch,
 // whose waves all load first and multiply after.
 #include <math.h>

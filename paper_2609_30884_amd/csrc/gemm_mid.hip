@@ -1,5 +1,7 @@
-// bf16 projections of 17 to about a thousand token rows (a short prefix, the
-// new tokens of a decoding step).  There 256x256 tiles leave most CUs without
+// bf16 projections of 17 token rows and more (a short prefix, the new tokens of a
+// decoding step), up to where the large tiles win (mid_rows in api.cpp: about 600
+// rows of 7B shapes, 1800 of 1.5B, several thousand of small decoders, fewer with
+// large adapters).  There 256x256 tiles leave most CUs without
 // one and the weights, read once, are a large share of the time, so the tiles
 // are 128 weight rows x 64 or 128 tokens, two or three workgroups per CU, and
 // K is split over workgroups until every CU has its share.

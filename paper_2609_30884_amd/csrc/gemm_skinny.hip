@@ -17,8 +17,8 @@
 // layer of a decoding step is a chain of launches whose start and end cost as
 // much as their bytes, so each one saved is worth 3 to 5 us.  A 7B-shaped layer
 // over a 16384-token prefix (rank 16 on all seven) takes 9 launches where it
-// took 14; whole step of 28 layers and a 152064-row head, 15.2 GB: 4.62 -> 3.95
-// ms (3.8 TB/s); 1.5B shapes, 5 tokens over 3001: 2.18 -> 1.86 ms.  The head
+// took 14; whole step of 28 layers and a 152064-row head, 15.2 GB: 4.62 -> 3.99
+// ms (3.8 TB/s); 1.5B shapes, 5 tokens over 3001: 2.22 -> 1.87 ms.  The head
 // alone streams at 6.2 TB/s, gate/up at 5.1, down at 4.9, QKV at 2.6 (33 MB in
 // 13 us: about 6 us of every launch are its start and end).
 #include <algorithm>

@@ -87,7 +87,8 @@ struct GemmParams {
   int N;                       // rows of the (virtual) weight matrix in tile space
   const bf16 *w[3];            // segment row sources, each [rows, K]
   int seg1, seg2;              // EPI_QKV: first rows of the k and v segments
-  // LoRA delta: acc += U[:, ucol_s : ucol_s + kpad] * lb_s^T  per segment s
+  // LoRA delta: acc += U[:, ucol_s : ucol_s + kpad] * lb_s^T  per segment s (few
+  // token rows: U comes as upart below)
   const bf16 *U;
   int ldu, kpad, rank;
   const bf16 *lb[3];           // [seg_rows, rank] or nullptr
@@ -119,10 +120,10 @@ struct GemmParams {
   const float *upart;
   int upart_n, upart_cols;
   float uscale;
-  // EPI_RESID: when the tiles leave the last wave of the grid at most half
-  // full (n_cu compute units), the last tiles are split into K-parts that
-  // write fp32 partials to split_part (split_cap floats) and a second kernel
-  // adds them to the residual in a fixed order.  split_first / split_s are
+  // EPI_RESID, EPI_QKV: when the tiles leave the last wave of the grid at most
+  // half full (n_cu compute units; two thirds with a long K), the last tiles are
+  // split into K-parts that write fp32 partials to split_part (split_cap floats)
+  // and a second kernel adds them up in a fixed order.  split_first / split_s are
   // set by the launcher.
   float *split_part;
   int64_t split_cap;
@@ -170,7 +171,7 @@ struct NormLora {
 int norm_lora_parts(int d);
 hipError_t launch_norm_lora(hipStream_t s, bool x_f32, const NormLora &p, int n_blocks);
 
-// ---- 17 to MID_MAX_ROWS token rows (gemm_mid.hip)
+// ---- 17 token rows and more, up to where the 256x256 tiles win (gemm_mid.hip)
 constexpr int MID_SEGS = 6;       // row sources of a launch: up to three weights, then their A factors
 constexpr int MID_MAX_COLS = 8192;  // widest residual row of reduce_resid
 // Y = X W^T over the concatenated rows [0, N) of the segments (each a multiple
@@ -227,8 +228,9 @@ hipError_t launch_mid_reduce_resid(hipStream_t s, const MidReduce &p);
 inline float attn_query_scale(int hd) { return 1.4426950408889634f / __builtin_sqrtf((float)hd); }
 // Query rows 0..Mq-1 at positions q_off..q_off+Mq-1 over keys 0..q_off+Mq-1,
 // Q pre-multiplied by attn_query_scale(hd).
-// part (nullable, part_floats floats): workspace for splitting a few query
-// rows (<= 16) over the keys of a long prefix.  With `lora` (Mq <= 16) and a
+// part (nullable, part_floats floats): workspace for splitting the keys over
+// workgroups: of a few query rows or blocks over a long prefix, or of a window's
+// longest blocks.  With `lora` (Mq <= 16) and a
 // split launch the merge also forms the parts of O A^T, one per query head
 // (lora->n_parts set; else it stays 0).
 struct AttnLora {

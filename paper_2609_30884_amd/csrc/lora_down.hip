@@ -179,7 +179,9 @@ hipError_t go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, int *n_part
   // until there are about two to a CU, of at least 16 k-steps.  777 tokens of 7B
   // shapes, rank 32: down (K = 18944) 85 -> 19 us, o (K = 3584) 22 -> 8, gate/up
   // 22 -> 12.  Two parts of 256 token blocks are slower than none (4096 tokens of
-  // 1.5B shapes, q/k/v: 12.4 against 11.2 us).
+  // 1.5B shapes, q/k/v: 12.4 against 11.2 us), three of 129 to 170 faster (a layer of
+  // 7B shapes, rank 64 on all: 2064 tokens 1269 -> 1206 us, 2720: 1573 -> 1514; rank 16
+  // on q, k, v, o: the same within 1 %).
   const int mb = (a.M + 15) / 16;
   const int64_t cap = lw.blocks ? lw.floats / ((int64_t)mb * NB * 256) : 0;
   const int64_t split = std::min<int64_t>({512 / mb, nsteps / 16, cap, 64});
