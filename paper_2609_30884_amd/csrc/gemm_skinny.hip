@@ -288,12 +288,6 @@ __global__ __launch_bounds__(256) void norm_lora_kernel(const NormLora p) {
     for (int b = 0; b < NB; ++b)
       ab[u][b] = as_bf16x8(on[b] && k < kend ? ld16(arow[b] + k) : u32x4{0u, 0u, 0u, 0u});
   };
-  // this wave's rows of the slice, on their way while the squares are summed
-  const int c0 = k0 + 8 * lane;
-  float own[4][8];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (wave + 4 * q < p.M && c0 < kend) load8f(x + (int64_t)(wave + 4 * q) * p.d + c0, own[q]);
   // Squares: every thread takes 8 columns in 2048, for four rows at a time.  The
   // first rows' loads go out ahead of the factors', whose wait would hold them.
   float ss[4] = {0.f, 0.f, 0.f, 0.f};
@@ -323,16 +317,15 @@ __global__ __launch_bounds__(256) void norm_lora_kernel(const NormLora p) {
       }
   }
   __syncthreads();
-  if (c0 < kend) {  // (a wave covers the slice)
+  {
+    const int c = k0 + 8 * lane;  // a wave covers the slice
     float gv[8];
-    load8f(p.g + c0, gv);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int m = wave + 4 * q;
-      if (m >= p.M) break;  // uniform
-      const float (&v)[8] = own[q];
+    if (c < kend) load8f(p.g + c, gv);
+    for (int m = wave; m < p.M && c < kend; m += 4) {
+      float v[8];
+      load8f(x + (int64_t)m * p.d + c, v);
       if (p.copy_out) {
-        float *o = p.copy_out + (int64_t)m * p.d + c0;
+        float *o = p.copy_out + (int64_t)m * p.d + c;
         *reinterpret_cast<f32x4 *>(o) = f32x4{v[0], v[1], v[2], v[3]};
         *reinterpret_cast<f32x4 *>(o + 4) = f32x4{v[4], v[5], v[6], v[7]};
       }
@@ -340,7 +333,7 @@ __global__ __launch_bounds__(256) void norm_lora_kernel(const NormLora p) {
       bf16x8 o;
 #pragma unroll
       for (int i = 0; i < 8; ++i) o[i] = f2bf(v[i] * r * gv[i]);
-      st16(p.y + (int64_t)m * p.d + c0, as_u32x4(o));
+      st16(p.y + (int64_t)m * p.d + c, as_u32x4(o));
       st16(&xs[m][8 * lane], as_u32x4(o));
     }
   }
