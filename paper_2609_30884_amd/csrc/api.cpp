@@ -443,9 +443,21 @@ crf_status run_layers_mid(crf_context *ctx, const void *hb, const crf_layer_weig
 // 861, 700 tokens 907 / 888; d = 768, d_ffn = 2048, rank 64 on all, one layer, 2500
 // tokens 220 / 228, 8192 tokens 593 / 430.
 // Past two rounds of 256x256 gate/up tiles the large tiles' whole rounds win.
+// From 13 rows on they also take calls whose gate/up adapters are large: every
+// weight-streaming gate/up workgroup sums all parts of both U (57 KB at rank 64 of
+// 7B shapes).  Two layers, rank 64 on all, 16 rows: 7B shapes 458 -> 414 us, 1.5B
+// 202 -> 186, d = 768 152 -> 136; rank 16 on all: 394 -> 345, 155 -> 147, and d = 768
+// (4 KB) 113 against 112, 109 against 112 at 14 rows.
+constexpr int MID_MIN_ROWS = 13, MID_MIN_U = 96;  // columns of U times parts
+
 bool mid_rows(const crf_context *ctx, int rows, const crf_lora_layer *lora, int l0, int h) {
   const crf_model_dims &d = ctx->dims;
-  if (rows <= 16 || d.d_model > MID_MAX_COLS || ctx->n_cu <= 0) return false;
+  if (rows < MID_MIN_ROWS || d.d_model > MID_MAX_COLS || ctx->n_cu <= 0) return false;
+  if (rows <= 16) {
+    bool gate_up = false;
+    for (int l = l0; l < l0 + h; ++l) gate_up |= has_lora(lora, l, CRF_GATE) || has_lora(lora, l, CRF_UP);
+    if (!gate_up || 2 * ctx->rank_pad * norm_lora_parts(d.d_model) < MID_MIN_U) return false;
+  }
   const int64_t D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn;
   const int64_t tiles = (int64_t)((rows + 255) / 256) * ((2 * f + 255) / 256);
   const int64_t cols = std::max<int64_t>(dq + 2 * dkv, D) + 3 * ctx->max_rank;
@@ -619,8 +631,8 @@ crf_status run_layers_few(crf_context *ctx, const void *hb, const crf_layer_weig
 crf_status run_layers_bf16(crf_context *ctx, const void *hb, const crf_layer_weights *W,
                            const crf_lora_layer *lora, int l0, int h, const crf_kv_cache *kv, void *hout,
                            hipStream_t s, int rows, int pos0, bool kv_tail) {
-  if (rows <= 16) return run_layers_few(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
   if (mid_rows(ctx, rows, lora, l0, h)) return run_layers_mid(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
+  if (rows <= 16) return run_layers_few(ctx, hb, W, lora, l0, h, kv, hout, s, rows, pos0, kv_tail);
   const crf_model_dims &d = ctx->dims;
   const int M = rows, D = d.d_model, dq = dq_of(d), dkv = dkv_of(d), f = d.d_ffn, hd = d.head_dim;
   const int rp = ctx->rank_pad, ldu = 3 * rp;

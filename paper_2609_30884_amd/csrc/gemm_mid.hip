@@ -1,5 +1,5 @@
-// bf16 projections of 17 token rows and more (a short prefix, the new tokens of a
-// decoding step), up to where the large tiles win (mid_rows in api.cpp: about 600
+// bf16 projections of 17 token rows and more, with large adapters of 13 (a short
+// prefix, the new tokens of a decoding step), up to where the large tiles win (mid_rows in api.cpp: about 600
 // rows of 7B shapes, 1800 of 1.5B, several thousand of small decoders, fewer with
 // large adapters).  There 256x256 tiles leave most CUs without
 // one and the weights, read once, are a large share of the time, so the tiles

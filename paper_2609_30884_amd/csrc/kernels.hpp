@@ -63,9 +63,9 @@ struct LoraDownTarget {
 };
 // U[m, ucol_t + j] = bf16(scale_t * sum_k X[m,k] A_t[j,k]) for j < rank_pad(t)
 // (zero for rank <= j < rank_pad).
-// M <= 16: U is not formed; unscaled fp32 parts of it are left in ws
-// ([part][16][n_targets * rank_pad], ws_floats floats), *n_parts of them, for
-// the projection to sum.  M > 16: `lw` (nullable blocks) lets K be split over
+// With n_parts (M <= 16) U is not formed; unscaled fp32 parts of it are left in
+// ws ([part][16][n_targets * rank_pad], ws_floats floats), *n_parts of them, for
+// the projection to sum.  Without, `lw` (nullable blocks) lets K be split over
 // workgroups, in `floats` floats and n_tickets counters that are zero between
 // launches.
 struct LoraWs {
@@ -171,7 +171,7 @@ struct NormLora {
 int norm_lora_parts(int d);
 hipError_t launch_norm_lora(hipStream_t s, bool x_f32, const NormLora &p, int n_blocks);
 
-// ---- 17 token rows and more, up to where the 256x256 tiles win (gemm_mid.hip)
+// ---- 17 token rows and more (13 with large adapters), up to where the 256x256 tiles win (gemm_mid.hip)
 constexpr int MID_SEGS = 6;       // row sources of a launch: up to three weights, then their A factors
 constexpr int MID_MAX_COLS = 8192;  // widest residual row of reduce_resid
 // Y = X W^T over the concatenated rows [0, N) of the segments (each a multiple

@@ -153,12 +153,12 @@ template <int NB>
 hipError_t go(hipStream_t s, LdArgs a, float *ws, int64_t ws_floats, int *n_parts, const LoraWs &lw) {
   constexpr int UNROLL = NB <= 4 ? 8 : 2;
   const int nsteps = a.K / 32;
-  if (a.M <= 16) {
+  if (n_parts) {
     // a few token rows: K split over workgroups (one batch of loads per wave),
     // the parts summed by the projection that uses U
     a.spw = 4 * UNROLL;
     const int n = (nsteps + a.spw - 1) / a.spw;
-    if (!n_parts || !ws || (int64_t)n * 16 * a.n_targets * a.rank_pad > ws_floats) return hipErrorInvalidValue;
+    if (a.M > 16 || !ws || (int64_t)n * 16 * a.n_targets * a.rank_pad > ws_floats) return hipErrorInvalidValue;
     a.part = ws;
     *n_parts = n;
     hipLaunchKernelGGL((lora_down_kernel<NB, UNROLL, 1>), dim3(1, n), dim3(256), 0, s, a);

@@ -22,7 +22,13 @@ WINDOWS = {
     "n1_r16": (1, S64, 16, ALL),
     "n2_r40": (2, S128, 40, ALL),
     "n7_r8_vod": (7, S64, 8, ("v", "o", "down")),
+    "n12_r64": (12, S128, 64, ALL),
+    # 13 rows and more with large adapters on gate/up: the kernels of larger counts
+    "n13_r64": (13, S128, 64, ALL),
+    "n14_r24_up": (14, S128, 24, ("up", "down")),
     "n16_r64": (16, S128, 64, ALL),
+    # (too small an adapter: d = 640 has two parts of 2 x 16 columns)
+    "n16_r16": (16, S64, 16, ALL),
     "n4_none": (4, S128, 16, ()),
     "n5_none": (5, S128, 16, ()),
     "n13_none": (13, S64, 16, ()),
